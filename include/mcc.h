@@ -173,6 +173,10 @@ mcc_status mcc_mech_create(const mcc_mech_desc *desc, int device, mcc_mech **out
  * one wavefront (more registers, fewer cells per compute unit; built for
  * every shape), 2 two wavefronts (only where that is the library's choice;
  * MCC_ERR_INVALID_ARG otherwise).  Results are identical bit for bit.
+ * (Mechanisms integrated four cells to a wavefront -- at most 32 species and
+ * 128 reactions with dense_tail 0, or at most 96 species and 256 reactions
+ * with dense_tail 32 -- have one build of mcc_solve_step and of its taped and
+ * per-launch forms, which serves either value.)
  * reserved: zero. */
 typedef struct {
     int32_t dense_tail;
@@ -231,6 +235,14 @@ mcc_status mcc_debug_emulate_cell(const mcc_mech *mech, const double *k, const d
  * of the transposed system, x = (I - c J(y))^-T b (the reverse-mode step). */
 mcc_status mcc_debug_emulate_cell_adjoint(const mcc_mech *mech, const double *k, const double *y, double c,
                                           const double *b, double *f, double *x, int32_t *violations);
+
+/* Testing aid (host only): as mcc_debug_emulate_cell with the tables of the
+ * solver that integrates four cells per wavefront (small mechanisms, and
+ * those with a 32-row dense tail up to 96 species); *violations also counts
+ * writes of constant cells, and an entry read before it is written comes out
+ * as NaN.  MCC_ERR_MECH for a mechanism that solver does not take. */
+mcc_status mcc_debug_emulate_quad(const mcc_mech *mech, const double *k, const double *y, double c,
+                                  const double *b, double *f, double *x, int32_t *violations);
 
 /* Testing aid (host only): f and the sparse J of one cell from the tables of
  * the streaming f/J kernel, run on the host in the kernel's order; k

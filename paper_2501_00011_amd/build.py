@@ -17,7 +17,8 @@ ROOT = os.path.dirname(HERE)
 LIB_PATH = os.path.join(HERE, "libmcchem.so")
 OBJ_DIR = os.path.join(ROOT, "_build", "mcchem")
 SOURCES = ["csrc/api.hip", "csrc/kernels_fj.hip", "csrc/kernels_solve.hip", "csrc/mech_compile.cpp",
-           "csrc/mech_emulate.cpp", "csrc/fj_codegen.cpp", "csrc/kernels_paper.hip"]
+           "csrc/mech_emulate.cpp", "csrc/kernels_quad_dense.hip", "csrc/kernels_quad_front12.hip",
+           "csrc/kernels_quad_front34.hip", "csrc/fj_codegen.cpp", "csrc/kernels_paper.hip"]
 ARCH = os.environ.get("MCC_OFFLOAD_ARCH", "gfx950")
 
 # Packed FP32 instructions stay off: the library computes in FP64, and packed

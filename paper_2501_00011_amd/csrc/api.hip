@@ -33,6 +33,7 @@ struct mcc_mech {
     const uint16_t *fwd_map = nullptr, *bwd_map = nullptr;
     const uint16_t *schur_tab = nullptr;
     int32_t off_y = 0, off_k = 0, off_r = 0, off_p = 0, off_lu = 0, off_tm = 0, lds_doubles = 0;
+    QuadParams quad{};  // the quad solver's tables and sizes (t.quad.ok)
     int live_batches = 0;
     int solve_waves = 0;  // wavefronts per SIMD of the solver build launched
     // mechanism-specialised f/J kernel, compiled on first use
@@ -264,6 +265,11 @@ mcc_status mcc_mech_create_ex(const mcc_mech_desc *desc, int device, const mcc_m
         delete m;
         return hip_error(e, "hipDeviceGetAttribute");
     }
+    if (m->t.quad.ok && (int64_t)m->t.quad.stride * kQCells * 8 > max_lds) m->t.quad.ok = false;
+    if (m->t.quad.ok && (e = prepare_quad_kernels(m->t.quad, max_lds)) != hipSuccess) {
+        delete m;
+        return hip_error(e, "hipFuncSetAttribute");
+    }
     const size_t lds_bytes = (size_t)m->lds_doubles * sizeof(double);
     if (lds_bytes > (size_t)max_lds) {
         delete m;
@@ -301,6 +307,13 @@ mcc_status mcc_mech_create_ex(const mcc_mech_desc *desc, int device, const mcc_m
     const size_t oa_fg = pk.add(ta.fg_ops), oa_nm = pk.add(ta.nm_ops), oa_lu = pk.add(ta.lu_ops);
     const size_t oa_fwd = pk.add(ta.fwd_map), oa_bwd = pk.add(ta.bwd_map), oa_sch = pk.add(ta.schur_tab);
     const size_t oa_nup = pk.add(ta.nu_ptr), oa_nuv = pk.add(ta.nu_vid), oa_nuc = pk.add(ta.nu_coef);
+    const QuadTables &q = t.quad;
+    const size_t oq_vsp = pk.add(q.vsp), oq_rx = pk.add(q.rx), oq_fc = pk.add(q.fg_coef), oq_fi = pk.add(q.fg_idx);
+    const size_t oq_nm0 = pk.add(q.nm_dev[0]), oq_nm1 = pk.add(q.nm_dev[1]), oq_tm = pk.add(q.tmap), oq_fill = pk.add(q.fill[0]), oq_fill1 = pk.add(q.fill[1]);
+    const size_t oq_lu = pk.add(q.lu_dev), oq_lf = pk.add(q.lu_flags), oq_sch = pk.add(q.schur);
+    const size_t oq_fwd = pk.add(q.fwd), oq_bwt = pk.add(q.bwt);
+    const size_t oq_bwf = pk.add(q.bwf), oq_dm = pk.add(q.dmap);
+    const size_t oq_ml = pk.add(q.mid_load), oq_ms = pk.add(q.mid_store);
     if ((e = hipMalloc(&m->dev_buf, pk.bytes.size())) != hipSuccess) {
         delete m;
         return hip_error(e, "hipMalloc (mechanism tables)");
@@ -344,6 +357,45 @@ mcc_status mcc_mech_create_ex(const mcc_mech_desc *desc, int device, const mcc_m
     m->adj.nu_ptr = (const int32_t *)(b + oa_nup);
     m->adj.nu_vid = (const int32_t *)(b + oa_nuv);
     m->adj.nu_coef = (const double *)(b + oa_nuc);
+    if (q.ok) {
+        QuadParams &p = m->quad;
+        p.vsp = (const int32_t *)(b + oq_vsp);
+        p.rx = (const QRx *)(b + oq_rx);
+        p.fg_coef = (const double *)(b + oq_fc);
+        p.fg_idx = (const uint16_t *)(b + oq_fi);
+        p.nm[0] = (const uint32_t *)(b + oq_nm0);
+        p.nm[1] = (const uint32_t *)(b + oq_nm1);
+        p.tmap = (const uint16_t *)(b + oq_tm);
+        p.fill[0] = (const uint16_t *)(b + oq_fill);
+        p.fill[1] = (const uint16_t *)(b + oq_fill1);
+        p.lu = (const uint32_t *)(b + oq_lu);
+        p.lu_flags = (const uint32_t *)(b + oq_lf);
+        p.schur = (const QSchur *)(b + oq_sch);
+        p.fwd = (const uint16_t *)(b + oq_fwd);
+        p.bwt = (const uint16_t *)(b + oq_bwt);
+        p.bwf = (const uint16_t *)(b + oq_bwf);
+        p.dmap = (const uint16_t *)(b + oq_dm);
+        p.n_rx = q.n_rx;
+        p.fg_iters = q.fg_iters;
+        for (int e = 0; e < 2; ++e) {
+            p.nm_recs[e] = q.nm_recs[e];
+            p.nm_two[e] = q.nm_two[e];
+            p.nm_one[e] = q.nm_one[e];
+            p.n_fill[e] = q.n_fill[e];
+            p.n_lu[e] = q.n_lu[e];
+        }
+        p.split = q.split;
+        p.m0 = q.m0;
+        p.mid_load = (const uint16_t *)(b + oq_ml);
+        p.mid_store = (const uint16_t *)(b + oq_ms);
+        p.N = t.N;
+        p.R = t.R;
+        p.F = q.F;
+        p.Mt = q.Mt;
+        p.stride = q.stride;
+        p.off_r = q.off_r;
+        p.off_y = q.off_y;
+    }
     *out = m;
     return ok();
 }
@@ -382,6 +434,16 @@ mcc_status mcc_debug_emulate_cell_adjoint(const mcc_mech *m, const double *k, co
     if (!m || (!k && m->ta.R > 0) || !y || !b || !f || !x || !violations)
         return set_error(MCC_ERR_INVALID_ARG, "null argument");
     *violations = emulate_cell(m->ta, k, y, c, b, f, x);
+    return ok();
+}
+
+mcc_status mcc_debug_emulate_quad(const mcc_mech *m, const double *k, const double *y, double c, const double *b,
+                                  double *f, double *x, int32_t *violations)
+{
+    if (!m || (!k && m->t.R > 0) || !y || !b || !f || !x || !violations)
+        return set_error(MCC_ERR_INVALID_ARG, "null argument");
+    if (!m->t.quad.ok) return set_error(MCC_ERR_MECH, "the four-cells-per-wavefront solver does not take this mechanism's shape");
+    *violations = emulate_quad(m->t, k, y, c, b, f, x);
     return ok();
 }
 
@@ -952,6 +1014,31 @@ mcc_status mcc_replay_step(const mcc_cells *c, const double *y0, const double *t
     return ok();
 }
 
+// One launch of the outer step on the kernel that takes the mechanism's shape.
+static hipError_t launch_outer_step(const mcc_mech *m, const SolveParams &p, hipStream_t s)
+{
+    if (!m->t.quad.ok) return launch_solve(p, m->t.NS, m->t.M, p.tape ? 0 : m->solve_waves, s);
+    QuadParams q = m->quad;
+    q.order = p.order;
+    q.k = p.k;
+    q.y = p.y;
+    q.status = p.status;
+    q.stats = p.stats;
+    q.n_cells = p.n_cells;
+    q.ld = p.ld;
+    q.dt = p.dt;
+    q.opts = p.opts;
+    q.state = p.state;
+    q.pending = p.pending;
+    q.state_stride = p.state_stride;
+    q.call_id = p.call_id;
+    q.mc_slots = p.mc_slots;
+    q.tape = p.tape;
+    q.tape_len = p.tape_len;
+    q.tape_stride = p.tape_stride;
+    return launch_quad(m->t.quad, q, s);
+}
+
 static mcc_status solve_step(mcc_cells *c, double *y, double dt, const mcc_solver_opts *opts, int32_t *cell_status,
                              mcc_cell_stats *stats, double *tape, int64_t *tape_len, int64_t tape_stride, void *stream)
 {
@@ -976,14 +1063,14 @@ static mcc_status solve_step(mcc_cells *c, double *y, double dt, const mcc_solve
     p.tape_len = tape_len;
     p.tape_stride = tape_stride;
     if (o.steps_per_launch <= 0) {  // the whole outer step in one launch
-        hipError_t e = launch_solve(p, m->t.NS, m->t.M, p.tape ? 0 : m->solve_waves, (hipStream_t)stream);
+        hipError_t e = launch_outer_step(m, p, (hipStream_t)stream);
         if (e != hipSuccess) return hip_error(e, "solver kernel launch");
         return ok();
     }
     // Per-launch form: state in HBM between launches; relaunch until every
     // cell has finished.  Every launch takes each unfinished cell at least one
     // accepted step (or to its end), so max_steps / K + 1 launches suffice.
-    p.state_stride = (int64_t)(kMaxOrder + 3) * m->t.NV + kStateScalars;
+    p.state_stride = (int64_t)(kMaxOrder + 3) * (m->t.quad.ok ? m->t.quad.NB * kQLanes : m->t.NV) + kStateScalars;
     const int64_t need = p.state_stride * c->n_cells;
     hipStream_t s = (hipStream_t)stream;
     if (c->state_doubles < need) {
@@ -1009,7 +1096,7 @@ static mcc_status solve_step(mcc_cells *c, double *y, double dt, const mcc_solve
     for (int64_t launch = 0;; ++launch) {
         if (launch >= max_launches) return set_error(MCC_ERR_DEVICE, "per-launch solver did not finish");
         hipError_t e = launch_fill_i32(c->pending, 0, s);
-        if (e == hipSuccess) e = launch_solve(p, m->t.NS, m->t.M, p.tape ? 0 : m->solve_waves, s);
+        if (e == hipSuccess) e = launch_outer_step(m, p, s);
         if (e == hipSuccess) e = hipMemcpyAsync(c->pending_host, c->pending, sizeof(int32_t), hipMemcpyDeviceToHost, s);
         if (e == hipSuccess) e = hipStreamSynchronize(s);
         if (e != hipSuccess) return hip_error(e, "per-launch solver");

@@ -1,0 +1,7 @@
+// Quad solver kernels: see quad_kernel.hpp.
+#include "quad_launch.hpp"
+
+namespace mcc {
+MCC_QUAD_DEFINE(2, 32, 3, 16, 1)
+MCC_QUAD_DEFINE(2, 32, 4, 16, 1)
+}  // namespace mcc

@@ -96,6 +96,81 @@ struct VjpItem {
 constexpr int kVjpRoundLoads = 64;  // measured: 48-96 beat 16-32 at 200k cells, equal at 10k
 
 // ---------------------------------------------------------------------------
+// Tables of the four-cells-per-wavefront solver (kernels_quad.hip): a cell is
+// a row of 16 lanes, and every table is laid out for 16 lanes, shared by the
+// four cells.  Rows of the system live in blocks of 16: block f < FB holds the
+// front positions 16 f .. 16 f + 15, block FB + b the rows of the dense tail
+// 16 b ..; lane i holds row i of every block.  All index fields are 16-bit
+// indices (in doubles) into the cell's local memory.
+// ---------------------------------------------------------------------------
+constexpr int kQLanes = 16;  // lanes per cell
+constexpr int kQCells = kWave / kQLanes;
+// Local memory of a cell: fixed cells, the front's LU entries (structural
+// fill last), scratch (rates | rate partials | re-sampling matrix), y.
+constexpr int kQZero = 0, kQTrash = 1, kQOne = 2, kQFirst = 3;
+// Newton-matrix records, in this order: records of entries with more than two
+// terms (and of every diagonal entry), four terms of one entry each, what
+// becomes of the sum in dst[3]; records of two entries with two terms; records
+// of four entries with one term.  Each kind a multiple of four records.
+constexpr uint16_t kQNmMore = 0, kQNmLast = 1, kQNmDiag = 2;  // sum on; store; store 1 + it
+struct alignas(16) QNmRec {  // one lane's part of a Newton-matrix record
+    double coef[4];
+    uint16_t src[4];  // rate partials
+    uint16_t dst[4];  // LU or staging entries
+};
+// A front LU unit: four entries per lane, dst = (dst - sum of l u) * scale, or
+// its reciprocal (diagonals), at most kQLuSteps terms each.  Flags of a unit:
+// the terms in use, whether entry e of every lane is a diagonal (bit 4 + e),
+// whether the unit continues the previous one's sums, is continued.
+constexpr int kQLuSteps = 4, kQLuEnt = 4;
+constexpr uint32_t kQLuD = 16, kQLuCont = 256, kQLuMore = 512;
+struct alignas(16) QLuUnit {
+    uint16_t dst[kQLuEnt], scale[kQLuEnt];
+    uint16_t lu[kQLuSteps][kQLuEnt][2];
+};
+constexpr int kQMid = 48 + 32;  // the middle pivots' registers: 16 rows x (16 + 32) columns, 32 tail rows x 16 columns
+constexpr int kQAhead = 4;  // rows every streamed table is padded by: the kernel reads ahead of its use
+// One lane's part of a front pivot's Schur update: its L in tail blocks 0, 1;
+// its U in tail columns lane, 16 + lane.
+struct alignas(8) QSchur {
+    uint16_t l[2], u[2];
+};
+struct alignas(16) QRx {  // one lane's reaction of a round of 16
+    uint16_t y[3], r;     // reactants (the constant 1 where a slot is empty); where its rate goes
+    uint16_t d[3], pad1;  // where its rate partials go (the write-only cell if none)
+};
+struct QuadTables {
+    bool ok = false;
+    int TB = 0, NC = 0, FB = 0, NB = 0, F = 0, Mt = 0;  // blocks, tail columns (padded), front and tail sizes
+    int stride = 0, off_r = 0, off_y = 0;               // doubles
+    int n_rx = 0, fg_iters = 0, nbp = 0;
+    // The front's first `split` pivots are the sparse ones.  Everything they
+    // touch -- their own entries, and the tail's entries, staged in local
+    // memory -- is assembled and updated first; then the tail goes to
+    // registers and the other pivots' entries take the staging's place.
+    // The last (up to) 16 front positions, from m0 on, are nearly dense: after
+    // the units have applied the pivots before them they are eliminated in
+    // registers, as the tail is.
+    int split = 0, m0 = 0;
+    int nm_recs[2] = {0, 0}, nm_two[2] = {0, 0}, nm_one[2] = {0, 0};  // records; the first of two, one term
+    int n_fill[2] = {0, 0}, n_lu[2] = {0, 0};
+    std::vector<int32_t> vsp;          // [NB][16] species or -1
+    std::vector<QRx> rx;               // [round][lane]
+    std::vector<double> fg_coef;       // [iteration][block][lane][2]
+    std::vector<uint16_t> fg_idx;      // [iteration][lane][nbp][2]
+    std::vector<QNmRec> nm[2];         // [record][lane]: first and second part
+    std::vector<uint16_t> tmap;        // staged tail entry of (block, column): [e / 8][lane][8], e = block * NC + column
+    std::vector<uint16_t> fill[2];     // entries set to zero: [v][lane][8]
+    std::vector<QLuUnit> lu;           // [unit][lane], the first part's, then the second's
+    std::vector<uint32_t> lu_flags;    // [unit]
+    std::vector<uint32_t> nm_dev[2], lu_dev;  // nm and lu as the kernel reads them: [record][16-byte vector][lane]
+    std::vector<QSchur> schur;         // [pivot - split][lane], pivots split .. m0 - 1
+    std::vector<uint16_t> mid_load, mid_store;  // [v][lane][8], kQMid registers: see build_quad
+    std::vector<uint16_t> fwd, bwt, bwf;  // sweep maps, vectors of eight columns per lane (see build_quad)
+    std::vector<uint16_t> dmap;        // [FB][lane]: the front's 1 / U_kk
+};
+
+// ---------------------------------------------------------------------------
 // Host-side compiled mechanism (built once by compile_mechanism).
 // ---------------------------------------------------------------------------
 struct HostTables {
@@ -181,7 +256,15 @@ struct HostTables {
     int64_t lu_lower = 0, lu_upper = 0;  // strictly lower / upper nonzeros of the sparse factors
     int64_t lu_updates = 0;           // multiply-adds per factorisation
     mcc_op_counts counts{};           // algorithmic work per cell
+    QuadTables quad;                  // four-cells-per-wavefront solver (quad.ok: it takes this shape)
 };
+
+// Fills t->quad from the compiled order and the symbolic factors (lp, by
+// position, the tail block dense), for the shapes that solver takes.
+void build_quad(const mcc_mech_desc *d, const std::vector<std::vector<char>> &lp, HostTables *t);
+// Host emulation of the quad solver's phases for one cell (testing aid), as emulate_cell.
+int emulate_quad(const HostTables &t, const double *k, const double *y_species, double c, const double *b_species,
+                 double *f_species, double *x_species);
 
 // Validates desc and fills t.  Returns MCC_OK or MCC_ERR_MECH with *err set.
 // transpose: the solver tables are built for I - c J^T (reverse mode).
@@ -266,7 +349,42 @@ struct SolveParams {
     int64_t *tape_len;
     int64_t tape_stride;
 };
-constexpr int kStateScalars = 16;
+constexpr int kStateScalars = 24;
+
+// Kernel parameters of the quad solver (kernels_quad.hip); the fields from
+// `order` on mean what they do in SolveParams.
+struct QuadParams {
+    const int32_t *vsp;
+    const QRx *rx;
+    const double *fg_coef;
+    const uint16_t *fg_idx;
+    const uint32_t *nm[2], *lu;  // by 16-byte vector
+    const uint16_t *tmap, *fill[2];
+    const uint32_t *lu_flags;
+    const QSchur *schur;
+    const uint16_t *fwd, *bwt, *bwf, *dmap;
+    const uint16_t *mid_load, *mid_store;
+    int32_t n_rx, fg_iters, nm_recs[2], nm_two[2], nm_one[2], n_fill[2], n_lu[2], split, m0;
+    int32_t N, R, F, Mt, stride, off_r, off_y;
+    const int32_t *order;
+    const double *k;
+    double *y;
+    int32_t *status;
+    mcc_cell_stats *stats;
+    int64_t n_cells, ld;
+    double dt;
+    mcc_solver_opts opts;
+    double *state;
+    int32_t *pending;
+    int64_t state_stride;
+    int32_t call_id;
+    double *mc_slots;
+    double *tape;
+    int64_t *tape_len;
+    int64_t tape_stride;
+};
+hipError_t prepare_quad_kernels(const QuadTables &q, int max_lds_bytes);
+hipError_t launch_quad(const QuadTables &q, const QuadParams &p, hipStream_t s);
 
 // Step tapes: per cell, entries in time order, each [type, state (n_species
 // doubles, accepted steps only), order, value, type]; types 0 start (value:

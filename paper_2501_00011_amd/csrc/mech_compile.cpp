@@ -21,6 +21,7 @@
 #include <sstream>
 
 #include "mcc_internal.hpp"
+#include "quad_tables.hpp"
 
 namespace mcc {
 namespace {
@@ -742,6 +743,7 @@ mcc_status compile_mechanism(const mcc_mech_desc *d, int dense_tail, HostTables 
         oc.reserved = 0;
     }
 
+    build_quad(d, lp, t);
     return MCC_OK;
 }
 

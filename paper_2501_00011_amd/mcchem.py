@@ -77,6 +77,7 @@ def library(path: str = LIB_PATH) -> ctypes.CDLL:
         "mcc_debug_emulate_fj": ([vp, vp, vp, vp, vp, vp], ctypes.c_int),
         "mcc_debug_emulate_vjp": ([vp, vp, vp, vp, vp, vp, vp], ctypes.c_int),
         "mcc_debug_emulate_cell_adjoint": ([vp, vp, vp, dbl, vp, vp, vp, vp], ctypes.c_int),
+        "mcc_debug_emulate_quad": ([vp, vp, vp, dbl, vp, vp, vp, vp], ctypes.c_int),
         "mcc_mech_set_fj_kernel": ([vp, ctypes.c_int32], ctypes.c_int),
         "mcc_calc_vjp": ([vp, vp, vp, vp, vp, vp], ctypes.c_int),
         "mcc_adjoint_step": ([vp, vp, vp, vp, i64, vp, vp, i32, vp, vp], ctypes.c_int),
@@ -178,17 +179,20 @@ class Mechanism:
                  "fj_bytes", "f_bytes", "j_bytes"]
         return dict(zip(names, list(buf)[:7]))
 
-    def emulate_cell(self, k, y, c, b, transposed: bool = False):
+    def emulate_cell(self, k, y, c, b, transposed: bool = False, quad: bool = False):
         """Host emulation of the solver phases for one cell (testing aid):
         returns (f, x = (I - c J)^-1 b, violations), or with transposed the
-        solve with (I - c J)^T by the reverse-mode tables."""
+        solve with (I - c J)^T by the reverse-mode tables, or with quad the
+        phases of the four-cells-per-wavefront solver."""
         k = np.ascontiguousarray(k, dtype=np.float64)
         y = np.ascontiguousarray(y, dtype=np.float64)
         b = np.ascontiguousarray(b, dtype=np.float64)
         f = np.zeros(self.n_species)
         x = np.zeros(self.n_species)
         v = ctypes.c_int32()
-        fn = library().mcc_debug_emulate_cell_adjoint if transposed else library().mcc_debug_emulate_cell
+        L = library()
+        fn = (L.mcc_debug_emulate_quad if quad else
+              L.mcc_debug_emulate_cell_adjoint if transposed else L.mcc_debug_emulate_cell)
         _check(fn(self._h, k.ctypes.data, y.ctypes.data, float(c), b.ctypes.data, f.ctypes.data, x.ctypes.data,
                   ctypes.byref(v)))
         return f, x, v.value

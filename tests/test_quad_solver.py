@@ -1,0 +1,102 @@
+"""The four-cells-per-wavefront solver: its host-compiled tables run on the
+CPU (mcc_debug_emulate_quad) against the oracle's f and a dense solve, and the
+kernels on the GPU against the oracle, at the sizes where its shapes begin and
+end (blocks of 16 rows, 16 / 24 / 32 dense columns, one to four blocks of
+front positions, the last block full, nearly empty) and at batch sizes that
+leave rows of the last wavefront empty."""
+import numpy as np
+import pytest
+
+from paper_2501_00011_amd import mcchem, synth
+
+# species, dense tail: dense in registers up to 32 species; a 32-row tail behind 1 .. 64 front positions
+SHAPES = [(5, 0), (16, 0), (17, 0), (24, 0), (25, 0), (32, 0),
+          (33, 32), (36, 32), (48, 32), (49, 32), (64, 32), (65, 32), (72, 32), (80, 32), (81, 32), (96, 32)]
+
+
+@pytest.mark.parametrize("n,tail", SHAPES)
+def test_tables_against_oracle_and_dense_solve(n, tail):
+    """f within 1e-12 of its scale (the bound of the library's other f
+    checks); x = (I - c J)^-1 b within 1e-9 relative (norm) of LAPACK's
+    solve: the matrices' condition times 2^-53 leaves three digits to spare;
+    no index out of range, no constant cell written, nothing read before it
+    is written."""
+    oracle = pytest.importorskip("oracle")
+    m = synth.make_mechanism(n, 2 * n)
+    h = mcchem.Mechanism(m, device=-1, dense_tail=tail)
+    o = oracle.Oracle(m)
+    c = synth.make_cells(m, 1, seed=700 + n)
+    k = o.rate_constants(c.T, c.jscale)
+    fr, fs = o.deriv(k, c.y0)
+    J = o.jac(k, c.y0)[0]
+    J = np.asarray(J).reshape(n, n) if np.asarray(J).size == n * n else np.asarray(J)[..., 0]
+    rng = np.random.default_rng(n)
+    for step in (1e-6, 1e-3, 1.0):
+        b = rng.normal(size=n) * c.y0[:, 0]
+        f, x, bad = h.emulate_cell(k[:, 0], c.y0[:, 0], step, b, quad=True)
+        assert bad == 0
+        assert np.all(np.abs(f - fr[:, 0]) <= 1e-12 * fs[:, 0])
+        ref = np.linalg.solve(np.eye(n) - step * J, b)
+        assert np.linalg.norm(x - ref) <= 1e-9 * np.linalg.norm(ref)
+
+
+def test_shapes_it_does_not_take():
+    for n, tail in ((40, 0), (72, 48), (97, 32), (150, 64)):
+        h = mcchem.Mechanism(synth.make_mechanism(n, 2 * n), device=-1, dense_tail=tail)
+        with pytest.raises(mcchem.MccError, match="four-cells"):
+            h.emulate_cell(np.ones(h.n_reactions), np.ones(n), 1.0, np.ones(n), quad=True)
+    # more reactions than the kernels hold rate constants for
+    h = mcchem.Mechanism(synth.make_mechanism(20, 129), device=-1)
+    with pytest.raises(mcchem.MccError, match="four-cells"):
+        h.emulate_cell(np.ones(129), np.ones(20), 1.0, np.ones(20), quad=True)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,tail", SHAPES)
+def test_solve_parity_and_forms(n, tail):
+    """y(dt) within the library's bar of the oracle (1e-6 |y| + 1e2 atol) for
+    one to six cells, so that the last wavefront holds one to four; the
+    per-launch and the taping form give the same bits, and so does each cell
+    alone."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    oracle = pytest.importorskip("oracle")
+    dev = torch.device("cuda:0")
+    m = synth.make_mechanism(n, 2 * n)
+    h = mcchem.Mechanism(m, dense_tail=tail)
+    c = synth.make_cells(m, 6, seed=800 + n)
+    o = oracle.Oracle(m)
+    k = o.rate_constants(c.T, c.jscale)
+    yo, so, _ = o.solve(k, c.y0, 60.0)
+    up = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(dev)  # noqa: E731
+    ref = None
+    for cells in (6, 5, 1):
+        print(f"quad solver: {n} species, {cells} cells", flush=True)
+        b = mcchem.Cells(h, cells, cells + 1)
+        b.bind(up(c.T[:cells]), up(c.P[:cells]), up(c.jscale[:cells]))
+        y0 = torch.zeros((n, cells + 1), dtype=torch.float64, device=dev)
+        y0[:, :cells] = up(c.y0[:, :cells])
+        y = y0.clone()
+        st, stats = b.step(y, 60.0)
+        torch.cuda.synchronize()
+        yg = y.cpu().numpy()
+        assert np.array_equal(st.cpu().numpy(), so[:cells]) and np.all(so == 0)
+        assert np.all(np.abs(yg[:, :cells] - yo[:, :cells]) <= 1e-6 * np.abs(yo[:, :cells]) + 1e2)
+        assert np.all(yg[:, cells] == 0.0)  # nothing written beyond the cells
+        ref = yg if ref is None else ref
+        assert np.array_equal(yg[:, :cells], ref[:, :cells])
+        if cells == 5:
+            y2 = y0.clone()
+            st2, stats2 = b.step(y2, 60.0, mcchem.default_opts(steps_per_launch=7))
+            assert torch.equal(y2, y) and torch.equal(st2, st) and torch.equal(stats2, stats)
+            tape = torch.empty((cells, 4 + 2000 * (n + 12)), dtype=torch.float64, device=dev)
+            tlen = torch.empty(cells, dtype=torch.int64, device=dev)
+            y3 = y0.clone()
+            b.step_taped(y3, 60.0, tape, tlen)
+            assert torch.equal(y3, y) and int(tlen.min()) > 0
+            y4, _ = b.replay_step(y0, tape, tlen)
+            torch.cuda.synchronize()
+            # the replay solves each step to convergence: within the Newton tolerance of the solve
+            assert np.all(np.abs(y4.cpu().numpy()[:, :cells] - yg[:, :cells]) <= 1e-7 * np.abs(yg[:, :cells]) + 1e1)
+        b.close()

@@ -61,15 +61,21 @@ class _SolveStep(torch.autograd.Function):
         k = torch.exp(lnk).contiguous()
         cells.set_rate_constants(k)
         y0 = y0.contiguous()
+        C, N = cells.n_cells, cells.mech.n_species
+        tape_len = torch.empty(C, dtype=torch.int64, device=y0.device)
+        tape = _first_tape(C, N, stride, y0.device)
         while True:
             y = y0.clone()
-            tape = torch.empty((cells.n_cells, stride), dtype=torch.float64, device=y0.device)
-            tape_len = torch.empty(cells.n_cells, dtype=torch.int64, device=y0.device)
             status, _ = cells.step_taped(y, dt, tape, tape_len, opts)
-            if cells.n_cells == 0 or int(tape_len.min()) >= 0:
+            shortest, longest = torch.stack(torch.aminmax(tape_len)).tolist() if C else (0, 0)
+            if shortest >= 0:
                 break
-            stride *= 2  # a tape did not fit: the same step again with room for it
+            need = 2 * tape.shape[1]  # a tape did not fit: the same step again with room for it
+            del tape
+            tape = torch.empty((C, need), dtype=torch.float64, device=y0.device)
         _check_forward(status)
+        if stride is None and 2 * longest < tape.shape[1]:
+            tape = tape[:, :longest].contiguous()  # what is kept until backward: the steps taken
         ctx.save_for_backward(y0, k, tape, tape_len)
         ctx.cells = cells
         return y
@@ -90,11 +96,26 @@ class _SolveStep(torch.autograd.Function):
 def solve_step(cells: "mcchem.Cells", y0: torch.Tensor, lnk: torch.Tensor, dt: float,
                opts: "mcchem.SolverOpts | None" = None, tape_stride: int | None = None) -> torch.Tensor:
     """y(dt) [N][ld] from y0 [N][ld] with rate constants exp(lnk) [R][ld].
-    tape_stride: doubles of step tape per cell (default room for about 256
-    steps; doubled and the step redone when a tape does not fit)."""
-    N = cells.mech.n_species
-    stride = tape_stride or 4 + 256 * (N + 16)
-    return _SolveStep.apply(y0, lnk, cells, dt, opts, stride)
+    tape_stride: doubles of step tape per cell (default room for 256 to 4096
+    steps, by the number of cells, cut to the longest tape afterwards; doubled and
+    the step redone when a tape does not fit)."""
+    return _SolveStep.apply(y0, lnk, cells, dt, opts, tape_stride or None)
+
+
+def _first_tape(n_cells: int, n_species: int, stride: "int | None", device) -> torch.Tensor:
+    """The tape of the first attempt.  A second attempt costs a whole solve, the
+    cut to the longest tape only a copy (72 species, 1,000 cells, forward and
+    backward pass: 76 ms, and 170 ms with room for 256 steps and two
+    doublings), so it starts with room for 4,096 steps, at most 2 GiB in all
+    and at least 256 steps, and with the 256 alone where memory is short."""
+    if stride is not None:
+        return torch.empty((n_cells, stride), dtype=torch.float64, device=device)
+    per_step = n_species + 16
+    steps = min(4096, max(256, (2 << 30) // (8 * max(n_cells, 1) * per_step)))
+    try:
+        return torch.empty((n_cells, 4 + steps * per_step), dtype=torch.float64, device=device)
+    except torch.cuda.OutOfMemoryError:
+        return torch.empty((n_cells, 4 + 256 * per_step), dtype=torch.float64, device=device)
 
 
 def _tape_bound(stats, n_species: int) -> int:

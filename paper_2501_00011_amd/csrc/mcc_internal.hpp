@@ -105,6 +105,7 @@ constexpr int kVjpRoundLoads = 64;  // measured: 48-96 beat 16-32 at 200k cells,
 // ---------------------------------------------------------------------------
 constexpr int kQLanes = 16;  // lanes per cell
 constexpr int kQCells = kWave / kQLanes;
+constexpr int kQLdsBytes = 160 * 1024;  // local memory of a compute unit
 // Local memory of a cell: fixed cells, the front's LU entries (structural
 // fill last), scratch (rates | rate partials | re-sampling matrix), y.
 constexpr int kQZero = 0, kQTrash = 1, kQOne = 2, kQFirst = 3;

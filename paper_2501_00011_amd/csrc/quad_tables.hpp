@@ -254,7 +254,11 @@ void build_quad(const mcc_mech_desc *d, const std::vector<std::vector<char>> &lp
     const int total = q.off_y + F + q.TB * L;
     q.stride = (total + 15) / 16 * 16;
     if (q.stride / 16 % 2 == 0) q.stride += 16;  // an odd multiple of 16 doubles: neighbour cells start on other banks
-    if ((int64_t)q.stride * 8 * kQCells > 65536 * 2 || q.stride > 0x1fff) return;
+    // Three wavefronts' cells have to fit a compute unit's local memory: with
+    // 12 to 16 cells there the solve of 10,000 cells took 135 ms against 163 ms
+    // of the one-cell kernels (72 species, 151 reactions, tail of 32), with 8
+    // cells 601 ms against 505 ms (96 species, 201 reactions).
+    if ((int64_t)q.stride * 8 * kQCells * 3 > kQLdsBytes) return;
     auto yid = [&](int species) { return q.off_y + t->iperm[species]; };
 
     // ---- reactions -----------------------------------------------------------

@@ -418,7 +418,7 @@ mcc_status mcc_solve_step_multicell(mcc_cells *cells, double *y, double dt, cons
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc):
  * mcc_solve_step_multicell with the grid-wide reduction slots in a
- * statically allocated device array of the library (256 KiB per device,
+ * statically allocated device array of the library (512 KiB per device,
  * held until the process ends) instead of memory the batch allocates on
  * first use.  Arguments, results and errors as mcc_solve_step_multicell;
  * MCC_ERR_INVALID_ARG for more than 16,384 cells.  The call itself

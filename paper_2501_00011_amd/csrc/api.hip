@@ -67,7 +67,7 @@ struct mcc_cells {
     int32_t *pending = nullptr;
     int32_t *pending_host = nullptr;  // pinned
     int32_t call_id = 0;
-    double *mc_slots = nullptr;  // Multi-cells reduction slots [2][mc_cells]
+    double *mc_slots = nullptr;  // Multi-cells reduction slots, for mc_cells cells
     int64_t mc_cells = 0;
     int32_t *order = nullptr;    // the solver's cell schedule (device [n_cells]), or null
 };
@@ -1014,10 +1014,8 @@ mcc_status mcc_replay_step(const mcc_cells *c, const double *y0, const double *t
     return ok();
 }
 
-// One launch of the outer step on the kernel that takes the mechanism's shape.
-static hipError_t launch_outer_step(const mcc_mech *m, const SolveParams &p, hipStream_t s)
+static QuadParams quad_params(const mcc_mech *m, const SolveParams &p)
 {
-    if (!m->t.quad.ok) return launch_solve(p, m->t.NS, m->t.M, p.tape ? 0 : m->solve_waves, s);
     QuadParams q = m->quad;
     q.order = p.order;
     q.k = p.k;
@@ -1036,7 +1034,14 @@ static hipError_t launch_outer_step(const mcc_mech *m, const SolveParams &p, hip
     q.tape = p.tape;
     q.tape_len = p.tape_len;
     q.tape_stride = p.tape_stride;
-    return launch_quad(m->t.quad, q, s);
+    return q;
+}
+
+// One launch of the outer step on the kernel that takes the mechanism's shape.
+static hipError_t launch_outer_step(const mcc_mech *m, const SolveParams &p, hipStream_t s)
+{
+    if (!m->t.quad.ok) return launch_solve(p, m->t.NS, m->t.M, p.tape ? 0 : m->solve_waves, s);
+    return launch_quad(m->t.quad, quad_params(m, p), s);
 }
 
 static mcc_status solve_step(mcc_cells *c, double *y, double dt, const mcc_solver_opts *opts, int32_t *cell_status,
@@ -1105,8 +1110,8 @@ static mcc_status solve_step(mcc_cells *c, double *y, double dt, const mcc_solve
     return ok();
 }
 
-// The Multi-cells outer step; slots: caller-provided reduction slots
-// [2][n_cells] (the allocation-free entry point), or null for the batch's own.
+// The Multi-cells outer step; slots: caller-provided reduction slots (the
+// allocation-free entry point), or null for the batch's own.
 static mcc_status solve_step_multicell(mcc_cells *c, double *y, double dt, const mcc_solver_opts *opts,
                                        int32_t *cell_status, mcc_cell_stats *stats, double *slots, void *stream);
 
@@ -1158,18 +1163,25 @@ static mcc_status solve_step_multicell(mcc_cells *c, double *y, double dt, const
     if (c->n_cells > cap)
         return set_error(MCC_ERR_INVALID_ARG, "Multi-cells needs every cell resident at once: at most " +
                                                   std::to_string(cap) + " cells of this mechanism on this device");
+    // The four-cells kernels take the batches they can hold at once (one cell
+    // alone then has the bits of its own solve; figures at their exchange in
+    // quad_kernel.hpp), the one-cell kernels the rest.
+    int64_t quad_cap = 0;
+    e = quad_multicell_capacity(m->t.quad, m->device, &quad_cap);
+    if (e != hipSuccess) return hip_error(e, "Multi-cells occupancy");
     if (!slots && c->mc_cells < c->n_cells) {
         if (c->mc_slots) (void)hipFree(c->mc_slots);
         c->mc_slots = nullptr;
         c->mc_cells = 0;
-        e = hipMalloc(&c->mc_slots, 2 * (size_t)c->n_cells * sizeof(double));
+        e = hipMalloc(&c->mc_slots, kMcSlotWords * ((size_t)c->n_cells + kQCells - 1) * sizeof(double));
         if (e != hipSuccess) return hip_error(e, "hipMalloc (Multi-cells reduction slots)");
         c->mc_cells = c->n_cells;
     }
     SolveParams p = solve_params(c, y, dt, o, cell_status, stats);
     p.order = nullptr;  // the grid-wide sums are taken in workgroup order: keep it the cell order
     p.mc_slots = slots ? slots : c->mc_slots;
-    e = launch_solve_multicell(p, m->t.NS, m->t.M, (hipStream_t)stream);
+    e = c->n_cells <= quad_cap ? launch_quad_multicell(m->t.quad, quad_params(m, p), (hipStream_t)stream)
+                               : launch_solve_multicell(p, m->t.NS, m->t.M, (hipStream_t)stream);
     if (e != hipSuccess) return hip_error(e, "Multi-cells solver launch");
     return ok();
 }

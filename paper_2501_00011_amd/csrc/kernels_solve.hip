@@ -27,12 +27,11 @@
 //   HBM       : y in/out, k in, status and stats out; in the per-launch form
 //               the solver state between launches; when taping, the step
 //               tape.
-#include <hip/hip_cooperative_groups.h>
 
 #include <map>
 #include <mutex>
 
-#include "mcc_internal.hpp"
+#include "grid_exchange.hpp"
 
 namespace mcc {
 namespace {
@@ -873,26 +872,27 @@ __device__ __forceinline__ void rescale_transposed(double (&L)[kMaxOrder + 3][NS
     }
 }
 
-// Multi-cells: sums over all cells of the launch (one workgroup per cell,
-// all co-resident: a cooperative launch).  Every wavefront publishes its
-// value in a slot of its own, waits at the grid barrier, then adds all slots
-// in one fixed order, so every wavefront obtains the same bits and takes the
-// same decisions.  Two slot arrays alternate: the barrier of reduction r + 1
-// separates reading r from writing r + 2.  Slots are read and written with
-// device-scope atomics, coherent across the XCDs' separate L2 caches.
-struct GridSum {
-    double *slots;  // [2][n]
-    int n, r;
-
-    __device__ __forceinline__ double sum(double v)  // v: the same on every lane
+// Norm sums and failure flags: of the cell, or (Multi-cells) over all cells.
+template <bool MC>
+struct GridSums {
+    __device__ __forceinline__ GridSums(double *, int) {}
+    __device__ __forceinline__ double sum(double v) { return v; }
+    __device__ __forceinline__ bool any(bool b) { return b; }
+};
+template <>
+struct GridSums<true> {
+    GridExchange<1> grid;
+    __device__ __forceinline__ GridSums(double *slots, int n) : grid(slots, n) {}
+    __device__ __forceinline__ double sum(double v)
     {
-        double *b = slots + (size_t)(r & 1) * n;
-        if (threadIdx.x == 0) __hip_atomic_store(&b[blockIdx.x], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        cooperative_groups::this_grid().sync();
-        double acc = 0.0;
-        for (int i = (int)threadIdx.x; i < n; i += kWave) acc += __hip_atomic_load(&b[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        ++r;
-        return wave_sum(acc);
+        double a[1] = {v};
+        grid.sum(a, 0);
+        return a[0];
+    }
+    __device__ __forceinline__ bool any(bool b)
+    {
+        double a[1] = {0.0};
+        return grid.sum(a, b) != 0;
     }
 };
 
@@ -936,13 +936,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(W))) void bd
     Cell<NS, M> C(p, smem);
     const int lane = C.lane, N = p.N;
     // norms and failure flags: of this cell, or (Multi-cells) of the whole system
-    GridSum grid{p.mc_slots, (int)p.n_cells, 0};
+    GridSums<MC> grid(p.mc_slots, (int)p.n_cells);
     const double n_all = MC ? (double)N * (double)p.n_cells : (double)N;
     auto norm = [&](const double (&v)[NS], const double (&w)[NS]) -> double {
         const double q = C.ssq(v, w);
-        return sqrt((MC ? grid.sum(q) : q) / n_all);
+        return sqrt(grid.sum(q) / n_all);
     };
-    auto any_cell = [&](bool b) -> bool { return MC ? grid.sum(b ? 1.0 : 0.0) > 0.0 : b; };
+    auto any_cell = [&](bool b) -> bool { return grid.any(b); };
     const mcc_solver_opts &o = p.opts;
     const double dt = p.dt;
     const int maxord = o.max_order < 1 ? 1 : (o.max_order > kMaxOrder ? kMaxOrder : o.max_order);
@@ -1770,13 +1770,13 @@ hipError_t multicell_capacity(int NS, int M, size_t lds_bytes, int device, int64
     return e;
 }
 
-// Multi-cells reduction slots, [2][kMcScratchCells] doubles, for the entry
+// Multi-cells reduction slots, [kMcSlotWords][kMcScratchCells] words, for the entry
 // point that allocates nothing (mcc_solve_step_multicell_noalloc).  Every
-// device the library runs on holds its own copy (256 KiB) until the process
+// device the library runs on holds its own copy (512 KiB) until the process
 // ends.  Host code never passes the array's name to a kernel (on the host it
 // is only a stand-in for the symbol); it passes the device address that
 // hipGetSymbolAddress returned for the current device.
-static __device__ __align__(256) double scratch[2 * kMcScratchCells];
+static __device__ __align__(256) double scratch[kMcSlotWords * kMcScratchCells];
 
 hipError_t multicell_scratch(int device, double **ptr)
 {

@@ -386,6 +386,9 @@ struct QuadParams {
 };
 hipError_t prepare_quad_kernels(const QuadTables &q, int max_lds_bytes);
 hipError_t launch_quad(const QuadTables &q, const QuadParams &p, hipStream_t s);
+// Its Multi-cells form (0 cells: not compiled for this shape).
+hipError_t quad_multicell_capacity(const QuadTables &q, int device, int64_t *max_cells);
+hipError_t launch_quad_multicell(const QuadTables &q, const QuadParams &p, hipStream_t s);
 
 // Step tapes: per cell, entries in time order, each [type, state (n_species
 // doubles, accepted steps only), order, value, type]; types 0 start (value:
@@ -453,9 +456,12 @@ hipError_t launch_fill_i32(int32_t *p, int32_t v, hipStream_t s);  // *p = v by 
 // Multi-cells solver: largest co-resident batch (0: no kernel for this shape), cooperative launch.
 hipError_t multicell_capacity(int NS, int M, size_t lds_bytes, int device, int64_t *max_cells);
 hipError_t launch_solve_multicell(const SolveParams &p, int NS, int M, hipStream_t s);
-// Statically allocated Multi-cells reduction slots ([2][kMcScratchCells]
-// doubles per device): the device address of the current device's copy,
-// looked up once per device (that device must be current).
+// Multi-cells reduction slots, 64-bit words per cell: two arrays of one value
+// (two words) per cell, or of four values per wavefront of four cells.
+constexpr int kMcSlotWords = 4;
+// Statically allocated slots ([kMcSlotWords][kMcScratchCells] words per
+// device): the device address of the current device's copy, looked up once
+// per device (that device must be current).
 constexpr int64_t kMcScratchCells = 16384;
 hipError_t multicell_scratch(int device, double **ptr);
 

@@ -106,3 +106,47 @@ def test_solve_parity_and_forms(n, tail):
             # the replay solves each step to convergence: within the Newton tolerance of the solve
             assert np.all(np.abs(y4.cpu().numpy()[:, :cells] - yg[:, :cells]) <= 1e-7 * np.abs(yg[:, :cells]) + 1e1)
         b.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,cells", [(5, 1), (16, 3), (16, 257), (17, 4), (24, 130), (32, 65), (40, 257)])
+def test_multicell(n, cells):
+    """One system over all cells, at batch sizes around a full wavefront (four
+    cells) and around what a wavefront's lanes read of the others' sums at a
+    time (16 wavefronts of four values, 256 of the one-cell kernels, which take
+    40 species): the oracle's shared step sequence and y(dt) within the
+    library's bar, every call with the same bits, and one cell with those of
+    its own solve."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    oracle = pytest.importorskip("oracle")
+    dev = torch.device("cuda:0")
+    m = synth.make_mechanism(n, 2 * n)
+    h = mcchem.Mechanism(m, dense_tail=0)
+    c = synth.make_cells(m, cells, seed=900 + n)
+    o = oracle.Oracle(m)
+    k = o.rate_constants(c.T, c.jscale)
+    yo, so, sto = o.solve_multicell(k, c.y0, 20.0)
+    up = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(dev)  # noqa: E731
+    print(f"Multi-cells: {n} species, {cells} cells", flush=True)
+    b = mcchem.Cells(h, cells)
+    b.bind(up(c.T), up(c.P), up(c.jscale))
+    y0 = up(c.y0)
+    out = []
+    for call in (dict(), dict(), dict(noalloc=True)):
+        y = y0.clone()
+        st, stats = b.step_multicell(y, 20.0, **call)
+        torch.cuda.synchronize()
+        assert so == 0 and int(st.abs().max()) == 0
+        out.append((y, stats))
+    assert all(torch.equal(out[0][0], y) and torch.equal(out[0][1], s) for y, s in out[1:])
+    yg, sn = out[0][0].cpu().numpy(), mcchem.stats_numpy(out[0][1])
+    assert np.all(np.abs(yg - yo) <= 1e-6 * np.abs(yo) + 1e2)
+    assert np.all(sn["steps"] == sn["steps"][0])
+    assert abs(int(sn["steps"][0]) - int(sto["steps"])) <= 0.05 * int(sto["steps"]) + 2
+    if cells == 1:
+        y = y0.clone()
+        st, stats = b.step(y, 20.0)
+        assert torch.equal(y, out[0][0]) and torch.equal(stats, out[0][1])
+    b.close()

@@ -34,7 +34,7 @@ SOLVE_SOURCES = ["paper_2501_00011_amd/csrc/kernels_solve.hip", "paper_2501_0001
                  "paper_2501_00011_amd/csrc/mech_compile.cpp"]
 FJ_SOURCES = ["paper_2501_00011_amd/csrc/fj_codegen.cpp", "paper_2501_00011_amd/csrc/mcc_internal.hpp",
               "paper_2501_00011_amd/csrc/mech_compile.cpp", "paper_2501_00011_amd/csrc/api.hip"]
-FJ_KERNEL = "mcc_fj_generated2"  # the two-cell variant (even leading dimension)
+FJ_KERNEL = "mcc_fj_generated2"  # the two-cell variant
 VJP_KERNEL = "mcc_vjp_generated2"
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic_medium10k.txt")
 

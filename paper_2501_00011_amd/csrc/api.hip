@@ -607,53 +607,54 @@ mcc_status mcc_cells_rate_constants(const mcc_cells *c, const double **k)
     return ok();
 }
 
-static bool aligned16(const void *p) { return p == nullptr || ((uintptr_t)p & 15) == 0; }
-
 // Memory-side cache of the MI355X (Infinity Cache), bytes.
 constexpr int64_t kMallBytes = (int64_t)256 << 20;
 
-// Launches a generated kernel over cells [0, n_cells): the two-cell variant
-// (fn2) over whole pairs when ld is even and every array is 16-byte aligned,
-// the one-cell variant (fn) over the rest.  arrays: the kernel's pointer
-// arguments in order (null allowed for an unused output).  in_rows: input
-// rows the kernel reads per cell; stream_grp: grp_tiles (see the generated
-// kernel head) once the inputs exceed the memory-side cache.  While the
-// inputs fit in that cache the items of a tile run together (grp_tiles 1:
-// one fetch per tile, later items hit the XCD's L2).  Beyond it the f/J
-// kernel, whose reads are a fifth of its traffic, runs each item over 128
-// consecutive tiles at once (16) so that the first reads of every row are
-// long runs: 55% of HBM peak instead of 44% at 200,000 cells of 72 species;
-// the VJP kernel, mostly reads, keeps 1 (its items then reuse the XCD's L2;
-// 16 measured slower).
+// Launches a generated kernel over cells [0, n_cells).  arrays: the kernel's
+// pointer arguments in order (null allowed for an unused output).  in_rows:
+// input rows the kernel reads per cell; streams: the kernel mostly writes and
+// gains from long runs of its reads once the inputs exceed the memory-side
+// cache.  72 species, 156 reactions, f/J kernel unless noted:
+// - up to 512 cells (eight tiles, one for each XCD): one cell per lane, the
+//   shorter chain (400 cells, in a graph: 3.5 us, two per lane 3.8);
+// - beyond, two cells per lane, whatever the rows' alignment (10,001 cells:
+//   23.9 us, one cell per lane 28.4);
+// - an odd leading dimension: rows begin anywhere in a cache line, and the
+//   lines at a tile's ends, written by two tiles, cost more than the rest.
+//   256 lanes per workgroup once there are 64 such tiles or more (eight per
+//   XCD: the uneven rest is small) take three quarters of these ends away:
+//   130,001 cells 275 us, 64 lanes 301, one cell per lane 375; VJP kernel
+//   146, 156 and 187 us;
+// - even, inputs within the memory-side cache: 64 lanes, all items of a tile
+//   together (one fetch per tile, later items hit the XCD's L2): 100,000
+//   cells 131 us, 256 lanes 140;
+// - even, beyond it: the f/J kernel, whose reads are a fifth of its traffic,
+//   in groups of 32 tiles of 256 lanes, so that the first reads of every row
+//   are long runs (200,000 cells: 409 us, 128 tiles of 64 lanes 413, 64 lanes
+//   without groups 505); the VJP kernel, mostly reads, as within the cache
+//   (its items reuse the XCD's L2).
 static mcc_status launch_generated(hipFunction_t fn, hipFunction_t fn2, std::vector<const void *> arrays,
                                    int64_t n_cells, int64_t ld, int item_begin, int n_items, int in_rows,
-                                   int stream_grp, void *stream)
+                                   bool streams, void *stream)
 {
     if (n_items == 0 || n_cells == 0) return ok();
-    bool pair = ld % 2 == 0;
-    for (const void *a : arrays) pair = pair && aligned16(a);
-    const int64_t n_pair_cells = pair ? n_cells / 2 * 2 : 0;
-    const bool streaming = 8 * (int64_t)in_rows * n_cells > kMallBytes;
-    auto go = [&](hipFunction_t f, int64_t lanes, int64_t c_begin, int64_t n_end) -> mcc_status {
-        if (lanes <= 0) return ok();
-        const int64_t n_tiles = (lanes + 63) / 64;
-        const int grp = streaming ? (int)std::max<int64_t>(1, std::min<int64_t>(stream_grp, (n_tiles + 7) / 8)) : 1;
-        const int64_t blocks = (n_tiles + 8 * grp - 1) / (8 * grp) * 8 * grp * n_items;
-        if (blocks > 0x7fffffff) return set_error(MCC_ERR_INVALID_ARG, "too many cells for one launch");
-        std::vector<void *> args;
-        for (const void *&a : arrays) args.push_back((void *)&a);
-        long long nc = n_end, ldl = ld, cb = c_begin;
-        int ib = item_begin, ni = n_items, nt = (int)n_tiles, gt = grp;
-        for (void *a : {(void *)&nc, (void *)&ldl, (void *)&cb, (void *)&ib, (void *)&ni, (void *)&nt, (void *)&gt})
-            args.push_back(a);
-        hipError_t e = hipModuleLaunchKernel(f, (unsigned)blocks, 1, 1, 64, 1, 1, 0, (hipStream_t)stream, args.data(),
-                                             nullptr);
-        if (e != hipSuccess) return hip_error(e, "generated kernel launch");
-        return ok();
-    };
-    mcc_status st = go(fn2, n_pair_cells / 2, 0, n_pair_cells);
-    if (st != MCC_OK) return st;
-    return go(fn, n_cells - n_pair_cells, n_pair_cells, n_cells);
+    const bool pair = n_cells > 8 * kWave, odd = ld % 2 != 0;
+    const int64_t lanes = pair ? (n_cells + 1) / 2 : n_cells;
+    const bool groups = !odd && streams && 8 * (int64_t)in_rows * n_cells > kMallBytes;
+    const int threads = groups || (odd && lanes > 63 * 256) ? 256 : kWave;
+    const int64_t n_tiles = (lanes + threads - 1) / threads;
+    const int grp = groups ? (int)std::min<int64_t>(4, (n_tiles + 7) / 8) : 1;
+    const int64_t blocks = (n_tiles + 8 * grp - 1) / (8 * grp) * 8 * grp * n_items;
+    if (blocks > 0x7fffffff) return set_error(MCC_ERR_INVALID_ARG, "too many cells for one launch");
+    std::vector<void *> args;
+    for (const void *&a : arrays) args.push_back((void *)&a);
+    long long nc = n_cells, ldl = ld;
+    int ib = item_begin, ni = n_items, nt = (int)n_tiles, gt = grp;
+    for (void *a : {(void *)&nc, (void *)&ldl, (void *)&ib, (void *)&ni, (void *)&nt, (void *)&gt}) args.push_back(a);
+    const hipError_t e = hipModuleLaunchKernel(pair ? fn2 : fn, (unsigned)blocks, 1, 1, (unsigned)threads, 1, 1, 0,
+                                               (hipStream_t)stream, args.data(), nullptr);
+    if (e != hipSuccess) return hip_error(e, "generated kernel launch");
+    return ok();
 }
 
 // Code objects of generated kernels, compiled once per process for each
@@ -747,7 +748,7 @@ static mcc_status run_fj(const mcc_cells *c, const double *y, double *f, double 
     mcc_status st = ensure_fj_module(c->mech);
     if (st != MCC_OK) return st;
     return launch_generated(c->mech->fj_fn, c->mech->fj2_fn, {p.y, p.k, p.f, p.jac}, p.n_cells, p.ld, p.item_begin,
-                            p.n_items, t.N + t.R, 16, stream);
+                            p.n_items, t.N + t.R, true, stream);
 }
 
 mcc_status mcc_calc_vjp(const mcc_cells *c, const double *y, const double *v, double *gy, double *glnk,
@@ -763,7 +764,7 @@ mcc_status mcc_calc_vjp(const mcc_cells *c, const double *y, const double *v, do
     mcc_status st = ensure_fj_module(c->mech);
     if (st != MCC_OK) return st;
     return launch_generated(c->mech->vjp_fn, c->mech->vjp2_fn, {y, c->k, v, gy, glnk}, c->n_cells, c->ld, 0,
-                            (int)t.vjp_items.size(), 2 * t.N + t.R, 1, stream);
+                            (int)t.vjp_items.size(), 2 * t.N + t.R, false, stream);
 }
 
 mcc_status mcc_ablation_paper_deriv(const mcc_mech *m, int64_t n_cells, const double *y, const double *k,

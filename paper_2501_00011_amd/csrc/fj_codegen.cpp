@@ -12,6 +12,8 @@
 
 #include <algorithm>
 #include <cstdio>
+#include <iterator>
+#include <map>
 #include <set>
 #include <sstream>
 #include <string>
@@ -33,49 +35,50 @@ std::string lit(double v)
 }  // namespace
 
 // Token placeholders of the generated bodies, filled per variant: @V@ the
-// per-cell value type (double, or the two-cell pair d2), @L@ the row stride
-// in values (ld, or ld / 2), @Z@ a zero value.
+// per-cell value type (double, or the two-cell pair d2), @R@ / @W@ an input /
+// output array from the lane's cells on, indexed in doubles, @L@ the row
+// stride, @Z@ a zero value.
 namespace {
 
 std::string fill(std::string s, bool pair)
 {
     const std::pair<const char *, const char *> rep[] = {
-        {"@V@", pair ? "d2" : "double"}, {"@L@", pair ? "ldv" : "ld"}, {"@Z@", pair ? "d2{0.0, 0.0}" : "0.0"}};
+        {"@V@", pair ? "d2" : "double"}, {"@L@", pair ? "ldv" : "ld"}, {"@Z@", pair ? "d2{0.0, 0.0}" : "0.0"},
+        {"@R@", pair ? "const pairs" : "const double *__restrict__"}, {"@W@", pair ? "const pairs" : "double *__restrict__"}};
     for (const auto &r : rep)
         for (size_t at = s.find(r.first); at != std::string::npos; at = s.find(r.first, at)) s.replace(at, 3, r.second);
     return s;
 }
 
-// Kernel head: block -> (64-lane tile, work item).  Blocks come in groups
-// of 8 * grp_tiles tiles times n_items; within a group the order is item
-// major: block q of XCD xcd (bid = 8 q + xcd) runs item r / grp_tiles on tile
-// (group * grp_tiles + r % grp_tiles) * 8 + xcd, r = q mod (n_items *
+// Kernel head: block -> (tile of blockDim.x lanes, work item).  Blocks come
+// in groups of 8 * grp_tiles tiles times n_items; within a group the order is
+// item major: block q of XCD xcd (bid = 8 q + xcd) runs item r / grp_tiles on
+// tile (group * grp_tiles + r % grp_tiles) * 8 + xcd, r = q mod (n_items *
 // grp_tiles).  grp_tiles = 1 runs all items of a tile on one XCD, one tile
 // after the other (the inputs of a tile are fetched once and then served by
 // that XCD's L2); a larger grp_tiles runs each item over 8 * grp_tiles
 // consecutive tiles at about the same time, so that the first reads of every
 // row are long runs of consecutive cells.  One-cell variant: lane = cell
-// c_begin + tile * 64 + lane.  Pair variant: lane = cells 2c and 2c + 1 with
-// c = tile * 64 + lane, 16-byte accesses (the caller guarantees an even ld,
-// 16-byte aligned arrays and whole pairs: n_cells even).
+// tile * blockDim.x + lane.  Pair variant: lane = cells c and c + 1 with
+// c = 2 (tile * blockDim.x + lane), 16-byte accesses that need 8-byte
+// alignment only, so any leading dimension; the last pair of an odd n_cells
+// is shifted down by one cell, which two lanes then write with the same bits.
 std::string head(const char *name, const char *args, const char *ptrs, bool pair)
 {
     std::ostringstream o;
-    o << "extern \"C\" __global__ __launch_bounds__(64) void " << name << (pair ? "2" : "") << "(\n" << args
-      << ", long long n_cells, long long ld, long long c_begin, int item_begin, int n_items, int n_tiles,\n"
-      << "    int grp_tiles)\n"
+    o << "extern \"C\" __global__ __launch_bounds__(256) void " << name << (pair ? "2" : "") << "(\n" << args
+      << ", long long n_cells, long long ld, int item_begin, int n_items, int n_tiles, int grp_tiles)\n"
       << "{\n"
       << "    const int bid = blockIdx.x, xcd = bid & 7, q = bid >> 3;\n"
       << "    const int grp = q / (n_items * grp_tiles), r = q - grp * (n_items * grp_tiles);\n"
       << "    const int item = item_begin + r / grp_tiles, tile = (grp * grp_tiles + r % grp_tiles) * 8 + xcd;\n"
       << "    if (tile >= n_tiles) return;\n";
     if (pair)
-        o << "    const long long c = (long long)tile * 64 + threadIdx.x;  // pair index\n"
-          << "    if (2 * c + 1 >= n_cells) return;\n"
-          << "    const long long ldv = ld >> 1;\n"
-          << "    (void)c_begin;\n";
+        o << "    const long long c0 = 2 * ((long long)tile * blockDim.x + threadIdx.x), ldv = ld;\n"
+          << "    if (c0 >= n_cells || n_cells < 2) return;\n"
+          << "    const long long c = c0 + 1 < n_cells ? c0 : n_cells - 2;\n";
     else
-        o << "    const long long c = c_begin + (long long)tile * 64 + threadIdx.x;\n"
+        o << "    const long long c = (long long)tile * blockDim.x + threadIdx.x;\n"
           << "    if (c >= n_cells) return;\n";
     o << ptrs;
     return o.str();
@@ -86,14 +89,18 @@ std::string head(const char *name, const char *args, const char *ptrs, bool pair
 std::string generate_preamble()
 {
     return "// generated per mechanism; d2 = the values of two adjacent cells\n"
-           "struct __attribute__((aligned(16))) d2 { double x, y; };\n"
+           "struct __attribute__((aligned(8))) d2 { double x, y; };\n"
            "__device__ __forceinline__ d2 operator+(d2 a, d2 b) { return d2{a.x + b.x, a.y + b.y}; }\n"
            "__device__ __forceinline__ d2 operator*(d2 a, d2 b) { return d2{a.x * b.x, a.y * b.y}; }\n"
            "__device__ __forceinline__ d2 operator*(double s, d2 b) { return d2{s * b.x, s * b.y}; }\n"
            "__device__ __forceinline__ d2 &operator+=(d2 &a, d2 b) { a.x += b.x; a.y += b.y; return a; }\n"
            "// outputs are stored non-temporally: no kernel reads them back soon\n"
            "__device__ __forceinline__ void st_out(double *p, double x) { __builtin_nontemporal_store(x, p); }\n"
-           "typedef double d2v __attribute__((ext_vector_type(2)));\n"
+           "typedef double d2v __attribute__((ext_vector_type(2), aligned(8)));\n"
+           "struct pairs {\n"
+           "    double *p;\n"
+           "    __device__ __forceinline__ d2 &operator[](long long i) const { return *(d2 *)(p + i); }\n"
+           "};\n"
            "__device__ __forceinline__ void st_out(d2 *p, d2 x) { __builtin_nontemporal_store(d2v{x.x, x.y}, (d2v *)p); }\n";
 }
 
@@ -105,10 +112,10 @@ std::string generate_fj_source(const HostTables &t, bool pair)
       << head("mcc_fj_generated",
               "    const double *__restrict__ y, const double *__restrict__ k, double *__restrict__ f,\n"
               "    double *__restrict__ jac",
-              "    const @V@ *__restrict__ Y = (const @V@ *)y + c;\n"
-              "    const @V@ *__restrict__ K = (const @V@ *)k + c;\n"
-              "    @V@ *__restrict__ F = (@V@ *)f + c;\n"
-              "    @V@ *__restrict__ G = (@V@ *)jac + c;\n",
+              "    @R@ Y{const_cast<double *>(y) + c};\n"
+              "    @R@ K{const_cast<double *>(k) + c};\n"
+              "    @W@ F{f + c};\n"
+              "    @W@ G{jac + c};\n",
               pair)
       << "    switch (item) {\n";
 
@@ -128,6 +135,16 @@ std::string generate_fj_source(const HostTables &t, bool pair)
         }
         for (int j : ks) o << "        const @V@ k" << j << " = K[" << j << " * @L@];\n";
         for (int r : ys) o << "        const @V@ y" << r << " = Y[" << r << " * @L@];\n";
+        // rows whose sum comes in parts, and the parts still to come: the sum
+        // stays in a register until it is whole
+        std::map<uint32_t, int> parts;
+        for (int ci = t.fj_items[it]; ci < t.fj_items[it + 1]; ++ci)
+            for (int r = 0; r < t.fj_chunks[ci].n_rec; ++r) {
+                const uint32_t meta = t.fj_recs[t.fj_chunks[ci].rec_begin + r].meta;
+                if ((meta >> 24) & kFjStore) parts[meta & kFjRowMask]++;
+            }
+        for (auto p = parts.begin(); p != parts.end();) p = p->second > 1 ? std::next(p) : parts.erase(p);
+        for (const auto &p : parts) o << "        @V@ s" << p.first << ";\n";
         for (int ci = t.fj_items[it]; ci < t.fj_items[it + 1]; ++ci) {
             const FjChunk &ch = t.fj_chunks[ci];
             o << "        {\n";
@@ -160,10 +177,12 @@ std::string generate_fj_source(const HostTables &t, bool pair)
                 if (flags & kFjStore) {
                     const std::string dst = row < (uint32_t)N ? "F[" + std::to_string(row) + " * @L@]"
                                                               : "G[" + std::to_string(row - N) + " * @L@]";
-                    if (flags & kFjAdd)
-                        o << "            " << dst << " += acc;\n";  // a later part of a split sum
-                    else
+                    if (!parts.count(row)) {
                         o << "            st_out(&" << dst << ", acc);\n";
+                        continue;
+                    }
+                    o << "            s" << row << ((flags & kFjAdd) ? " += acc;\n" : " = acc;\n");
+                    if (--parts[row] == 0) o << "            st_out(&" << dst << ", s" << row << ");\n";
                 }
             }
             o << "            (void)acc;\n        }\n";
@@ -191,11 +210,11 @@ std::string generate_vjp_source(const HostTables &t, bool pair)
               "    const double *__restrict__ y, const double *__restrict__ k, const double *__restrict__ v,\n"
               "    double *__restrict__ gy, double *__restrict__ glnk",
               "    const bool want_gy = gy != nullptr, want_glnk = glnk != nullptr;\n"
-              "    const @V@ *__restrict__ Y = (const @V@ *)y + c;\n"
-              "    const @V@ *__restrict__ K = (const @V@ *)k + c;\n"
-              "    const @V@ *__restrict__ V = (const @V@ *)v + c;\n"
-              "    @V@ *__restrict__ GY = (@V@ *)gy + c;\n"
-              "    @V@ *__restrict__ GK = (@V@ *)glnk + c;\n",
+              "    @R@ Y{const_cast<double *>(y) + c};\n"
+              "    @R@ K{const_cast<double *>(k) + c};\n"
+              "    @R@ V{const_cast<double *>(v) + c};\n"
+              "    @W@ GY{gy + c};\n"
+              "    @W@ GK{glnk + c};\n",
               pair)
       << "    switch (item) {\n";
     for (size_t it = 0; it < t.vjp_items.size(); ++it) {

@@ -1,0 +1,103 @@
+"""The generated f/J and VJP kernels at the sizes where their launch changes:
+one cell a lane or two, 64 lanes a workgroup or 256, an odd last cell (its
+pair shifted down, alone in a workgroup or not), rows and arrays that begin
+off a 16-byte boundary, and rows whose sum comes in parts."""
+import numpy as np
+import pytest
+
+from paper_2501_00011_amd import mcchem, synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch():
+    t = pytest.importorskip("torch")
+    if not t.cuda.is_available():
+        pytest.skip("no GPU")
+    return t
+
+
+def _check(torch, m, h, c, ld, shift):
+    """Against the oracle at the first and last cells (1e-12 of the sum of the
+    magnitudes of the terms, the library's bar: the longest sums here have some
+    140 terms of 2^-53 each), and at every other cell against the table-driven
+    kernel, which runs one cell a lane, within twice that bar."""
+    oracle = pytest.importorskip("oracle")
+    dev, C, N = torch.device("cuda:0"), c.n_cells, m.n_species
+
+    def array(rows, init=None):
+        a = torch.full((rows * ld + shift,), float("nan"), dtype=torch.float64, device=dev)[shift:].view(rows, ld)
+        if init is not None:
+            a[:, :C] = torch.from_numpy(np.ascontiguousarray(init)).to(dev)
+        return a
+
+    o = oracle.Oracle(m)
+    k = o.rate_constants(c.T, c.jscale)
+    b = mcchem.Cells(h, C, ld)
+    b.set_rate_constants(array(m.n_reactions, k).contiguous())
+    v0 = np.random.default_rng(5).normal(size=(N, C))
+    y, v = array(N, c.y0), array(N, v0)
+    f, J, gy, gk = array(N), array(h.nnz), array(N), array(m.n_reactions)
+    print(f"generated kernels: {N} species, {C} cells, ld {ld}, arrays shifted by {shift}", flush=True)
+    b.deriv_jac(y, f, J)
+    b.vjp(y, v, gy, gk)
+    h.set_fj_kernel(mcchem.Mechanism.FJ_TABLES)
+    f2, J2 = array(N), array(h.nnz)
+    b.deriv_jac(y, f2, J2)
+    h.set_fj_kernel(mcchem.Mechanism.FJ_GENERATED)
+    torch.cuda.synchronize()
+    host = [a.cpu().numpy() for a in (f, J, gy, gk, f2, J2)]
+    for a in host[:4]:
+        assert np.isnan(a[:, C:]).all()  # nothing written beyond the cells
+        assert np.isfinite(a[:, :C]).all()
+    f, J, gy, gk, f2, J2 = (a[:, :C] for a in host)
+    rp, ci = h.jac_pattern()
+    rows = np.repeat(np.arange(N), np.diff(rp))
+    sel = np.unique(np.r_[0:min(C, 130), max(0, C - 130):C])
+    fr, fs = o.deriv(k[:, sel], c.y0[:, sel])
+    Jr, Js = o.jac(k[:, sel], c.y0[:, sel])
+    gyr, gkr = o.vjp(k[:, sel], c.y0[:, sel], v0[:, sel])
+    assert np.all(np.abs(f[:, sel] - fr) <= 1e-12 * fs)
+    assert np.all(np.abs(J[:, sel] - Jr[:, rows, ci].T) <= 1e-12 * Js[:, rows, ci].T)
+    assert np.all(np.abs(gy[:, sel] - gyr) <= 1e-12 * np.einsum("ic,cis->sc", np.abs(v0[:, sel]), Js))
+    # r_j |w_j| at most r_j times the largest |v| times the number of terms and yields
+    r = np.empty((m.n_reactions, C))
+    nu = np.empty(m.n_reactions)
+    rate, used = np.zeros((N, C)), np.zeros((h.nnz, C))
+    for j in range(m.n_reactions):
+        reac = m.reac_idx[m.reac_ptr[j]:m.reac_ptr[j + 1]]
+        prod = m.prod_idx[m.prod_ptr[j]:m.prod_ptr[j + 1]]
+        yld = np.abs(m.prod_yield[m.prod_ptr[j]:m.prod_ptr[j + 1]])
+        r[j] = k[j] * np.prod(c.y0[reac], axis=0)
+        nu[j] = len(reac) + yld.sum()
+        for i, a in list(zip(reac, np.ones(len(reac)))) + list(zip(prod, yld)):
+            rate[i] += a * r[j]
+            for s in set(reac.tolist()):
+                e = rp[i] + np.searchsorted(ci[rp[i]:rp[i + 1]], s)
+                used[e] += a * r[j] * np.count_nonzero(reac == s) / c.y0[s]
+    assert np.all(np.abs(gk[:, sel] - gkr) <= 1e-12 * r[:, sel] * nu[:, None] * np.abs(v0[:, sel]).max(axis=0))
+    assert np.all(np.abs(f - f2) <= 2e-12 * rate)
+    assert np.all(np.abs(J - J2) <= 2e-12 * used)
+    b.close()
+
+
+@pytest.mark.parametrize("cells,ld,shift", [
+    (1, 1, 1), (2, 3, 0), (511, 511, 0), (512, 513, 1),   # one cell a lane
+    (513, 513, 0), (513, 514, 1), (514, 515, 0),          # two, the last pair shifted
+    (641, 641, 1),                                        # that pair alone in a workgroup of 64
+    (32255, 32257, 0), (32257, 32257, 0),                 # 64 and 256 lanes; the pair alone in a workgroup of 256
+])
+def test_launch_forms(torch, cells, ld, shift):
+    m = synth.make_mechanism(10, 20)
+    h = mcchem.Mechanism(m)
+    _check(torch, m, h, synth.make_cells(m, cells, seed=41), ld, shift)
+
+
+def test_rows_in_parts(torch):
+    """A row that 130 reactions form, more than a chunk of the tables holds."""
+    rx = [([i, i + 1], [(0, 1.0)], 1e-3 * (1 + i % 7), 0.0, 0) for i in range(1, 131)]
+    m = synth.mechanism_from_lists(140, rx)
+    h = mcchem.Mechanism(m)
+    c = synth.make_cells(m, 1025, seed=43)
+    _check(torch, m, h, c, 1027, 1)

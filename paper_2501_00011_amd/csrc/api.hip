@@ -31,7 +31,7 @@ struct mcc_mech {
     const Op16 *fg_ops = nullptr, *nm_ops = nullptr;
     const uint64_t *lu_ops = nullptr;
     const uint16_t *fwd_map = nullptr, *bwd_map = nullptr;
-    const uint16_t *schur_tab = nullptr;
+    const uint16_t *schur_tab = nullptr, *tail_map = nullptr;
     int32_t off_y = 0, off_k = 0, off_r = 0, off_p = 0, off_lu = 0, off_tm = 0, lds_doubles = 0;
     QuadParams quad{};  // the quad solver's tables and sizes (t.quad.ok)
     int live_batches = 0;
@@ -49,7 +49,7 @@ struct mcc_mech {
         const Op16 *fg_ops = nullptr, *nm_ops = nullptr;
         const uint64_t *lu_ops = nullptr;
         const uint16_t *fwd_map = nullptr, *bwd_map = nullptr;
-        const uint16_t *schur_tab = nullptr;
+        const uint16_t *schur_tab = nullptr, *tail_map = nullptr;
         int32_t off_y = 0, off_k = 0, off_r = 0, off_lu = 0, off_tm = 0, off_w = 0, lds_doubles = 0;
         std::string unavailable;  // empty: the reverse-mode kernel runs for this mechanism
     } adj;
@@ -208,8 +208,8 @@ mcc_status mcc_mech_create_ex(const mcc_mech_desc *desc, int device, const mcc_m
     m->off_r = m->off_k + t.R;
     m->off_p = m->off_r;
     m->off_tm = m->off_r;
-    m->off_lu = m->off_r + std::max({t.R + 1, t.n_partials + 1, kTm});
-    m->lds_doubles = m->off_lu + t.lu_nnz + 2;
+    m->off_lu = m->off_r + std::max({t.R + 1, t.n_partials + 1, kTm, tail_panel_doubles(t.M)});
+    m->lds_doubles = m->off_lu + t.lu_cells + 2;
     {
         // reverse mode: the same regions for the transposed tables, then R + 1 scratch values
         const HostTables &a = m->ta;
@@ -218,11 +218,11 @@ mcc_status mcc_mech_create_ex(const mcc_mech_desc *desc, int device, const mcc_m
         d.off_k = a.N + 1;
         d.off_r = d.off_k + a.R;
         d.off_tm = d.off_r;
-        d.off_lu = d.off_r + std::max({a.R + 1, a.n_partials + 1, kTm});
+        d.off_lu = d.off_r + std::max({a.R + 1, a.n_partials + 1, kTm, tail_panel_doubles(a.M)});
         // the R + 1 scratch values of the start entry, the last one reversed:
         // no factorisation follows, so they may take the LU storage
-        d.off_w = a.lu_nnz + 2 >= a.R + 1 ? d.off_lu : d.off_lu + a.lu_nnz + 2;
-        d.lds_doubles = std::max(d.off_lu + a.lu_nnz + 2, d.off_w + a.R + 1);
+        d.off_w = a.lu_cells + 2 >= a.R + 1 ? d.off_lu : d.off_lu + a.lu_cells + 2;
+        d.lds_doubles = std::max(d.off_lu + a.lu_cells + 2, d.off_w + a.R + 1);
         if (!adjoint_shape_supported(a.NS, a.M))
             d.unavailable = "no reverse-mode kernel for " + std::to_string(a.NS) + " species slots with a dense tail of " +
                             std::to_string(a.M);
@@ -301,11 +301,11 @@ mcc_status mcc_mech_create_ex(const mcc_mech_desc *desc, int device, const mcc_m
     const size_t o_preci = pk.add(t.paper_rec_inv), o_pyldi = pk.add(t.paper_yld_inv);
     const size_t o_perm = pk.add(t.vspecies), o_rxr = pk.add(t.rx_reac), o_part = pk.add(t.part);
     const size_t o_fg = pk.add(t.fg_ops), o_nm = pk.add(t.nm_ops), o_lu = pk.add(t.lu_ops);
-    const size_t o_fwd = pk.add(t.fwd_map), o_bwd = pk.add(t.bwd_map), o_sch = pk.add(t.schur_tab);
+    const size_t o_fwd = pk.add(t.fwd_map), o_bwd = pk.add(t.bwd_map), o_sch = pk.add(t.schur_tab), o_tmap = pk.add(t.tail_map);
     const HostTables &ta = m->ta;
     const size_t oa_perm = pk.add(ta.vspecies), oa_rxr = pk.add(ta.rx_reac), oa_part = pk.add(ta.part);
     const size_t oa_fg = pk.add(ta.fg_ops), oa_nm = pk.add(ta.nm_ops), oa_lu = pk.add(ta.lu_ops);
-    const size_t oa_fwd = pk.add(ta.fwd_map), oa_bwd = pk.add(ta.bwd_map), oa_sch = pk.add(ta.schur_tab);
+    const size_t oa_fwd = pk.add(ta.fwd_map), oa_bwd = pk.add(ta.bwd_map), oa_sch = pk.add(ta.schur_tab), oa_tmap = pk.add(ta.tail_map);
     const size_t oa_nup = pk.add(ta.nu_ptr), oa_nuv = pk.add(ta.nu_vid), oa_nuc = pk.add(ta.nu_coef);
     const QuadTables &q = t.quad;
     const size_t oq_vsp = pk.add(q.vsp), oq_rx = pk.add(q.rx), oq_fc = pk.add(q.fg_coef), oq_fi = pk.add(q.fg_idx);
@@ -345,6 +345,7 @@ mcc_status mcc_mech_create_ex(const mcc_mech_desc *desc, int device, const mcc_m
     m->fwd_map = (const uint16_t *)(b + o_fwd);
     m->bwd_map = (const uint16_t *)(b + o_bwd);
     m->schur_tab = (const uint16_t *)(b + o_sch);
+    m->tail_map = (const uint16_t *)(b + o_tmap);
     m->adj.vspecies = (const int32_t *)(b + oa_perm);
     m->adj.rx_reac = (const int32_t *)(b + oa_rxr);
     m->adj.part = (const int32_t *)(b + oa_part);
@@ -354,6 +355,7 @@ mcc_status mcc_mech_create_ex(const mcc_mech_desc *desc, int device, const mcc_m
     m->adj.fwd_map = (const uint16_t *)(b + oa_fwd);
     m->adj.bwd_map = (const uint16_t *)(b + oa_bwd);
     m->adj.schur_tab = (const uint16_t *)(b + oa_sch);
+    m->adj.tail_map = (const uint16_t *)(b + oa_tmap);
     m->adj.nu_ptr = (const int32_t *)(b + oa_nup);
     m->adj.nu_vid = (const int32_t *)(b + oa_nuv);
     m->adj.nu_coef = (const double *)(b + oa_nuc);
@@ -856,6 +858,7 @@ static SolveParams solve_params(mcc_cells *c, double *y, double dt, const mcc_so
     p.fwd_map = m->fwd_map;
     p.bwd_map = m->bwd_map;
     p.schur_tab = m->schur_tab;
+    p.tail_map = m->tail_map;
     p.schur_ks = m->t.schur_ks;
     for (int q = 0, base = 0; q < kMaxSlots; ++q) {
         p.fg_blocks[q] = q < m->t.NS ? m->t.fg_blocks[q] : 0;
@@ -871,7 +874,7 @@ static SolveParams solve_params(mcc_cells *c, double *y, double dt, const mcc_so
     p.N = m->t.N;
     p.R = m->t.R;
     p.P = m->t.n_partials;
-    p.lu_nnz = m->t.lu_nnz;
+    p.lu_nnz = m->t.lu_cells;
     p.off_y = m->off_y;
     p.off_k = m->off_k;
     p.off_r = m->off_r;
@@ -915,6 +918,7 @@ mcc_status mcc_adjoint_step(const mcc_cells *c, const double *y0, const double *
     p.fwd_map = m->adj.fwd_map;
     p.bwd_map = m->adj.bwd_map;
     p.schur_tab = m->adj.schur_tab;
+    p.tail_map = m->adj.tail_map;
     p.schur_ks = t.schur_ks;
     for (int q = 0, base = 0; q < kMaxSlots; ++q) {
         p.fg_blocks[q] = q < t.NS ? t.fg_blocks[q] : 0;
@@ -930,7 +934,7 @@ mcc_status mcc_adjoint_step(const mcc_cells *c, const double *y0, const double *
     p.N = t.N;
     p.R = t.R;
     p.P = t.n_partials;
-    p.lu_nnz = t.lu_nnz;
+    p.lu_nnz = t.lu_cells;
     p.off_y = m->adj.off_y;
     p.off_k = m->adj.off_k;
     p.off_r = m->adj.off_r;

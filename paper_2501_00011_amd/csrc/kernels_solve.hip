@@ -30,6 +30,7 @@
 
 #include <map>
 #include <mutex>
+#include <utility>
 
 #include "grid_exchange.hpp"
 
@@ -208,6 +209,17 @@ __device__ __forceinline__ void lds_fields8(const uint32_t (&w)[4], uint32_t bas
 
 typedef double v4d __attribute__((ext_vector_type(4)));
 
+template <class F, int... I>
+__device__ __forceinline__ void static_for_impl(std::integer_sequence<int, I...>, F &&f)
+{
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for(F &&f)
+{
+    static_for_impl(std::make_integer_sequence<int, N>{}, f);
+}
+
 template <int NS, int M>
 struct Cell {
     const SolveParams &p;
@@ -215,6 +227,9 @@ struct Cell {
     int lane;
     int N;
     bool vld[NS];
+    static constexpr bool kRegs = tail_in_registers(M);
+    static_assert(!kRegs || M == kWave, "a row of the tail in registers per lane");
+    double S[kRegs ? M : 1];  // kRegs: this lane's row of the tail's factors, 1/U_kk on the diagonal
 
     __device__ Cell(const SolveParams &pp, double *smem)
         : p(pp), yv(smem + pp.off_y), kv(smem + pp.off_k), rv(smem + pp.off_r), pv(smem + pp.off_p),
@@ -438,8 +453,13 @@ struct Cell {
             lds_handover();
         }
         const bool front_bad = __any(bad);
-        schur();
-        const bool tail_bad = dense_tail();
+        bool tail_bad;
+        if constexpr (kRegs) {
+            tail_bad = register_tail();
+        } else {
+            schur();
+            tail_bad = dense_tail();
+        }
         return front_bad || tail_bad;
     }
 
@@ -609,6 +629,152 @@ struct Cell {
         }
     }
 
+    // Schur complement and dense tail without the tail block in local memory
+    // (32 KB of a cell's 79 KB for 150 species, which let two cells run on a
+    // compute unit): the matrix-core accumulators start from the staged Jacobian
+    // entries, take all k-steps (each brings NT blocks of L and of U for its
+    // NT x NT products) and stay in registers as the trailing matrix of the
+    // blocked LU of dense_tail.  Per panel only its four columns and four rows
+    // pass through local memory; a factorised column is final on every row
+    // (rows above the panel: U, which the accumulators took up from the row
+    // phase), and each lane keeps its row of it in S, where the triangular
+    // solves read it.   The same
+    // bits as with the block in local memory; one attempt of 150 species 155
+    // -> 128 us and three cells a compute unit instead of two (1,000 cells 281
+    // -> 214 ms), of 110 species 65 -> 52 us and eight instead of three (108 ->
+    // 63 ms).
+    __device__ __forceinline__ bool register_tail()
+    {
+        KParams &p = params_here();
+        const int lane = lane_here();
+        const int g = lane >> 4, c16 = lane & 15;
+        const uint32_t lub = lds_base(lu);
+        v4d acc[NT][NT];
+        {
+            const uint4 *map = reinterpret_cast<const uint4 *>(p.tail_map) + lane;
+#pragma unroll
+            for (int v = 0; v < NT * NT / 2; ++v) {  // two tiles a vector of eight
+                const uint4 o = map[v * kWave];
+                const uint32_t w[4] = {o.x, o.y, o.z, o.w};
+                double x[8];
+                lds_fields8(w, lub, x);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) acc[(2 * v + e / 4) / NT][(2 * v + e / 4) % NT][e % 4] = x[e];
+            }
+        }
+        {
+            const int KS = p.schur_ks;
+            const uint4 *tab = reinterpret_cast<const uint4 *>(p.schur_tab) + lane;
+            uint4 nxt[SV];
+            if (KS > 0)
+#pragma unroll
+                for (int v = 0; v < SV; ++v) nxt[v] = tab[v * kWave];
+#pragma unroll 1
+            for (int k0 = 0; k0 < KS; k0 += SK) {
+                uint32_t w[4 * SV];
+#pragma unroll
+                for (int v = 0; v < SV; ++v) {
+                    w[4 * v] = nxt[v].x;
+                    w[4 * v + 1] = nxt[v].y;
+                    w[4 * v + 2] = nxt[v].z;
+                    w[4 * v + 3] = nxt[v].w;
+                }
+                if (k0 + SK < KS)
+#pragma unroll
+                    for (int v = 0; v < SV; ++v) nxt[v] = tab[(size_t)((k0 / SK + 1) * SV + v) * kWave];
+#pragma unroll
+                for (int kk = 0; kk < SK; ++kk) {  // k-steps beyond KS read the zero cell
+                    double a[NT], b[NT];
+#pragma unroll
+                    for (int i = 0; i < NT; ++i) a[i] = -lds_field(w, kk * 2 * NT + i, lub);
+#pragma unroll
+                    for (int j = 0; j < NT; ++j) b[j] = lds_field(w, kk * 2 * NT + NT + j, lub);
+#pragma unroll
+                    for (int i = 0; i < NT; ++i)
+#pragma unroll
+                        for (int j = 0; j < NT; ++j)
+                            acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
+                }
+            }
+        }
+        constexpr int ST = M + 4;
+        double *cb = rv, *rb = rv + 4 * ST;  // the panel's columns, [column][row]; its rows, [row][column]
+        int bad = 0;
+        static_for<M / 4>([&](auto PP) {
+            constexpr int k0 = 4 * decltype(PP)::value, t0 = k0 / 16, r0 = k0 % 16 / 4, kt = k0 + 4;
+            lds_handover();
+            if ((c16 & 12) == k0 % 16)
+#pragma unroll
+                for (int i = 0; i < NT; ++i)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) cb[(c16 & 3) * ST + 16 * i + 4 * r + g] = acc[i][t0][r];
+#pragma unroll
+            for (int j = t0; j < NT; ++j) rb[g * ST + 16 * j + c16] = acc[t0][j][r0];
+            lds_handover();
+            // panel: lane = row
+            double a[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) a[c] = cb[c * ST + lane];
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) {
+                const int k = k0 + kk;
+                const double ukk = lane_bcast(a[kk], k);
+                bad |= !(fabs(ukk) >= 1e-300) || !isfinite(ukk);
+                const double inv = pivot_rcp(ukk);
+                if (lane > k) {
+                    const double l = a[kk] * inv;
+                    a[kk] = l;
+#pragma unroll
+                    for (int c = kk + 1; c < 4; ++c) a[c] -= l * lane_bcast(a[c], k);
+                }
+                if (lane == k) a[kk] = inv;
+            }
+#pragma unroll
+            for (int c = 0; c < 4; ++c) S[k0 + c] = a[c];
+            if constexpr (kt < M) {
+                lds_handover();
+#pragma unroll
+                for (int c = 0; c < 4; ++c) cb[c * ST + lane] = a[c];
+                lds_handover();
+                // the panel's rows right of it (unit lower L11): lane = column
+                if (lane >= kt) {
+                    const double l10 = cb[k0 + 1], l20 = cb[k0 + 2], l30 = cb[k0 + 3];
+                    const double l21 = cb[ST + k0 + 2], l31 = cb[ST + k0 + 3], l32 = cb[2 * ST + k0 + 3];
+                    const double u0 = rb[lane];
+                    double u1 = rb[ST + lane], u2 = rb[2 * ST + lane], u3 = rb[3 * ST + lane];
+                    u1 -= l10 * u0;
+                    u2 -= l20 * u0;
+                    u2 -= l21 * u1;
+                    u3 -= l30 * u0;
+                    u3 -= l31 * u1;
+                    u3 -= l32 * u2;
+                    rb[ST + lane] = u1;
+                    rb[2 * ST + lane] = u2;
+                    rb[3 * ST + lane] = u3;
+                }
+                lds_handover();
+                // trailing update on the tiles that meet rows and columns >= kt
+                constexpr int t1 = kt / 16;
+                double af[NT], bf[NT];
+#pragma unroll
+                for (int q = t1; q < NT; ++q) {
+                    const bool in = 16 * q + c16 >= kt;
+                    const double x = cb[g * ST + 16 * q + c16], y = rb[g * ST + 16 * q + c16];
+                    af[q] = in ? -x : 0.0;  // L(row, k0 + g)
+                    bf[q] = in ? y : 0.0;   // U(k0 + g, column)
+                    acc[t0][q][r0] = in ? y : acc[t0][q][r0];
+                }
+#pragma unroll
+                for (int i = t1; i < NT; ++i)
+#pragma unroll
+                    for (int j = t1; j < NT; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(af[i], bf[j], acc[i][j], 0, 0, 0);
+            }
+        });
+        lds_handover();
+        return __any(bad);
+    }
+
     // b <- (LU)^-1 b with b held in registers by virtual index.  Columns are
     // swept in elimination order (front slots, then the tail in slot 0);
     // each column's value is broadcast from its lane with readlane.  For the
@@ -642,7 +808,7 @@ struct Cell {
                 for (int k8 = 0; k8 < M; k8 += 8) {
                     double tv[8];
 #pragma unroll
-                    for (int i = 0; i < 8; ++i) tv[i] = T[tat(trow, k8 + i)];
+                    for (int i = 0; i < 8; ++i) tv[i] = kRegs ? S[kRegs ? k8 + i : 0] : T[tat(trow, k8 + i)];
                     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                     for (int i = 0; i < 8; ++i) {
@@ -711,7 +877,7 @@ struct Cell {
                         for (int s = 1; s < NS; ++s) nxt[s] = bw[(size_t)(s * kWave + lane) * NVB + blk - 1];
                     double tv[8];  // 1/U_kk on the diagonal, U above it; loaded ahead as above
 #pragma unroll
-                    for (int i = 0; i < 8; ++i) tv[i] = T[tat(trow, blk * 8 + i)];
+                    for (int i = 0; i < 8; ++i) tv[i] = kRegs ? S[kRegs ? blk * 8 + i : 0] : T[tat(trow, blk * 8 + i)];
                     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                     for (int i = 7; i >= 0; --i) {

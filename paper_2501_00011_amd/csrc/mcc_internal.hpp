@@ -26,6 +26,12 @@ __host__ __device__ constexpr int tail_at(int M, int row, int col)
 {
     return col * M + (row ^ (4 * (col & tail_swizzle_mask(M))));
 }
+// Whether the solver holds the dense tail in registers instead (see
+// Cell::factor in kernels_solve.hip); local memory then stages only the
+// tail's Jacobian entries, and two buffers for a panel of four columns and of
+// four rows (each M + 4 apart).
+constexpr bool tail_in_registers(int M) { return M == 64; }
+constexpr int tail_panel_doubles(int M) { return tail_in_registers(M) ? 8 * (M + 4) : 0; }
 constexpr int kOffBits = 14;  // bits of an LDS offset inside an op
 constexpr uint32_t kOffMask = (1u << kOffBits) - 1;
 // flags of a Newton-matrix op (Op16::flags)
@@ -214,7 +220,13 @@ struct HostTables {
     std::vector<int32_t> vpos;        // [N]: virtual index of position p
     int NV = 0;                       // NS * 64
     int M = 0, F = 0;                 // dense tail size and front size (F = N - M)
-    int tail_base = 0;                // LU offset of the tail block (entry (i, j) at tail_base + tail_at(M, i, j))
+    int tail_base = 0;                // LU offset of the tail block (entry (i, j) at tail_base + tail_at(M, i, j)), or
+                                      // of its staged entries (tail_in_registers)
+    int lu_cells = 0;                 // LU entries in local memory (lu_nnz, or fewer with the tail in registers)
+    // tail_in_registers: offset of the staged entry that element e of lane l's
+    // accumulator tiles starts from (e = 4 (i nt + j) + r: entry (16 i + 4 r +
+    // l / 16, 16 j + l % 16)), or the zero cell, at (e / 8 * 64 + l) * 8 + e % 8
+    std::vector<uint16_t> tail_map;
     std::vector<int32_t> slot_cols;   // [NS]: columns (lanes) in use per slot
     // The solver's LDS copy of the state is compact: virtual index (slot s,
     // lane l) at ybase[s] + l, with ybase[s] the lanes in use of the slots
@@ -318,6 +330,7 @@ struct SolveParams {
     const uint64_t *lu_ops;
     const uint16_t *fwd_map, *bwd_map;
     const uint16_t *schur_tab;  // Schur complement operands (HostTables::schur_tab)
+    const uint16_t *tail_map;   // HostTables::tail_map
     int32_t schur_ks;
     int32_t fg_blocks[kMaxSlots], fg_base[kMaxSlots], slot_cols[kMaxSlots];
     int32_t ybase[kMaxSlots];  // compact LDS state vector: slot s at ybase[s] + lane

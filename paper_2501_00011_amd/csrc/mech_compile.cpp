@@ -517,11 +517,18 @@ mcc_status compile_mechanism(const mcc_mech_desc *d, int dense_tail, HostTables 
         for (int j = 0; j < N; ++j)
             if (lp[i][j] && !(i >= F && j >= F)) lpos[i][j] = nlu++;
     t->tail_base = nlu;
-    for (int j = F; j < N; ++j)
-        for (int i = F; i < N; ++i) lpos[i][j] = t->tail_base + tail_at(M, i - F, j - F);
-    nlu = t->tail_base + M * M;
-    t->lu_nnz = nlu;
-    if (nlu + 2 >= (1 << kOffBits)) {
+    t->lu_nnz = nlu + M * M;
+    if (tail_in_registers(M)) {  // the Jacobian's entries and the diagonal, staged
+        for (int i = F; i < N; ++i)
+            for (int j = F; j < N; ++j)
+                if (i == j || spat[t->perm[i]][t->perm[j]]) lpos[i][j] = nlu++;
+    } else {
+        for (int j = F; j < N; ++j)
+            for (int i = F; i < N; ++i) lpos[i][j] = t->tail_base + tail_at(M, i - F, j - F);
+        nlu = t->lu_nnz;
+    }
+    t->lu_cells = nlu;
+    if (t->lu_nnz + 2 >= (1 << kOffBits)) {
         *err = "LU fill exceeds the 14-bit offset range of the solver tables";
         return MCC_ERR_MECH;
     }
@@ -702,6 +709,17 @@ mcc_status compile_mechanism(const mcc_mech_desc *d, int dense_tail, HostTables 
             }
     }
 
+    t->tail_map.clear();
+    if (tail_in_registers(M)) {
+        const int nt = M / 16, n_map = (4 * nt * nt + 7) / 8 * 8;
+        t->tail_map.assign((size_t)n_map * kWave, (uint16_t)ZERO);
+        for (int lane = 0; lane < kWave; ++lane)
+            for (int e = 0; e < 4 * nt * nt; ++e) {
+                const int i = F + 16 * (e / 4 / nt) + 4 * (e % 4) + lane / 16, j = F + 16 * (e / 4 % nt) + lane % 16;
+                if (lpos[i][j] >= 0) t->tail_map[((size_t)(e / 8) * kWave + lane) * 8 + e % 8] = (uint16_t)lpos[i][j];
+            }
+    }
+
     // ---- solver: column maps for the triangular solves ---------------------
     // [slot][lane][v]: for the column at virtual index v, the offset of L(p,k)
     // (p after k) for the forward sweep, of U(p,k) (p before k) or of the
@@ -712,6 +730,7 @@ mcc_status compile_mechanism(const mcc_mech_desc *d, int dense_tail, HostTables 
     for (int pr = 0; pr < N; ++pr)
         for (int k = 0; k < N; ++k) {
             const size_t at = (size_t)vpos[pr] * t->NV + vpos[k];
+            if (tail_in_registers(M) && pr >= F && k >= F) continue;
             if (pr > k && lp[pr][k]) t->fwd_map[at] = (uint16_t)lpos[pr][k];
             if (pr <= k && lp[pr][k]) t->bwd_map[at] = (uint16_t)lpos[pr][k];
         }

@@ -21,9 +21,9 @@ int emulate_cell(const HostTables &t, const double *k, const double *y_species, 
                  const double *b_species, double *f_species, double *x_species)
 {
     const int N = t.N, R = t.R, P = t.n_partials, NS = t.NS, NV = t.NV, M = t.M;
-    const int ZERO = t.lu_nnz, TRASH = t.lu_nnz + 1;
+    const int ZERO = t.lu_cells, TRASH = t.lu_cells + 1;
     int bad = 0;
-    std::vector<double> yv(N + 1, 0.0), rv(R + 1, 0.0), pv(P + 1, 0.0), lu(t.lu_nnz + 2, 0.0);
+    std::vector<double> yv(N + 1, 0.0), rv(R + 1, 0.0), pv(P + 1, 0.0), lu(t.lu_cells + 2, 0.0);
     auto chk = [&](long v, long n) {
         if (v < 0 || v >= n) bad++;
         return v < 0 || v >= n ? 0 : v;
@@ -63,7 +63,7 @@ int emulate_cell(const HostTables &t, const double *k, const double *y_species, 
         d *= yv[chk(t.part[4 * q + 2], N + 1)];
         pv[q] = d;
     }
-    std::vector<int> written(t.lu_nnz + 2, 0);
+    std::vector<int> written(t.lu_cells + 2, 0);
     for (int lane = 0; lane < kWave; ++lane) {
         double acc = 0.0;
         for (int bk = 0; bk < t.nm_blocks; ++bk)
@@ -74,15 +74,15 @@ int emulate_cell(const HostTables &t, const double *k, const double *y_species, 
                 const double x = pv[chk(o.meta & 0xffff, P + 1)];
                 acc = (fl & kFirst) ? o.coef * x : acc + o.coef * x;
                 if (fl & kLast) {
-                    const int dst = chk(o.meta >> 16, t.lu_nnz + 2);
+                    const int dst = chk(o.meta >> 16, t.lu_cells + 2);
                     if (dst == ZERO) bad++;
-                    if (dst < t.lu_nnz) written[dst]++;
+                    if (dst < t.lu_cells) written[dst]++;
                     const double m = -c * acc;
                     lu[dst] = (fl & kDiag) ? 1.0 + m : m;
                 }
             }
     }
-    for (int e = 0; e < t.lu_nnz; ++e)
+    for (int e = 0; e < t.lu_cells; ++e)
         if (written[e] != 1) bad++;  // every LU entry is set exactly once
     lu[ZERO] = 0.0;
 
@@ -95,8 +95,8 @@ int emulate_cell(const HostTables &t, const double *k, const double *y_species, 
         for (int lane = 0; lane < kWave; ++lane)
             for (int i = 0; i < kBlk; ++i) {
                 const uint64_t w = t.lu_ops[((size_t)bk * kWave + lane) * kBlk + i];
-                const int dst = chk(w & kOffMask, t.lu_nnz + 2), l = chk((w >> 16) & kOffMask, t.lu_nnz + 2);
-                const int u = chk((w >> 32) & kOffMask, t.lu_nnz + 2), g = chk((w >> 48) & kOffMask, t.lu_nnz + 2);
+                const int dst = chk(w & kOffMask, t.lu_cells + 2), l = chk((w >> 16) & kOffMask, t.lu_cells + 2);
+                const int u = chk((w >> 32) & kOffMask, t.lu_cells + 2), g = chk((w >> 48) & kOffMask, t.lu_cells + 2);
                 if ((w >> 46) & 3 || (w >> 62) & 3) bad++;  // the u and 1/U_kk fields are bare indices
                 const double a0 = (w & kLuFirst) ? lu[dst] : acc[lane];
                 if (w & kLuScale) {
@@ -137,6 +137,18 @@ int emulate_cell(const HostTables &t, const double *k, const double *y_species, 
     }
     if (!step_writes.empty()) bad++;  // the last level must end with a barrier
 
+    // The tail block, from its places in the LU storage or from its staged
+    // entries (each read where the map says, the others zero).
+    const bool regs = tail_in_registers(M);
+    std::vector<std::vector<double>> a(M, std::vector<double>(M));
+    if (regs && t.tail_map.size() != (size_t)M * M) bad++;
+    for (int r = 0; r < M; ++r)
+        for (int q = 0; q < M; ++q) {
+            const int e = 4 * (r / 16 * (M / 16) + q / 16) + r % 16 / 4, lane = 16 * (r % 4) + q % 16;
+            const size_t at = ((size_t)(e / 8) * kWave + lane) * 8 + e % 8;
+            a[r][q] = lu[!regs ? t.tail_base + tail_at(M, r, q) : at < t.tail_map.size() ? (int)chk(t.tail_map[at], t.lu_cells + 1) : ZERO];
+        }
+
     // Schur complement onto the tail in 16 x 16 x 4 blocks, as the matrix
     // cores take them: for tile (I, J) and k-step ks, lane i + 16 kk holds
     // A(i, kk) and lane j + 16 kk holds B(kk, j); T(16 I + i, 16 J + j) -=
@@ -148,15 +160,15 @@ int emulate_cell(const HostTables &t, const double *k, const double *y_species, 
         auto opnd = [&](int ks, int q, int lane) {
             const int e = ks * 2 * nt + q;
             const size_t at = ((size_t)(e / 8) * kWave + lane) * 8 + e % 8;
-            const int o = at < t.schur_tab.size() ? (int)chk(t.schur_tab[at], t.lu_nnz + 1) : ZERO;
-            if (o >= t.tail_base && o < t.lu_nnz) bad++;  // an operand inside the tail block
+            const int o = at < t.schur_tab.size() ? (int)chk(t.schur_tab[at], t.lu_cells + 1) : ZERO;
+            if (o >= t.tail_base && o < t.lu_cells) bad++;  // an operand inside the tail block
             return lu[o];
         };
         for (int I = 0; I < nt; ++I)
             for (int J = 0; J < nt; ++J)
                 for (int i = 0; i < 16; ++i)
                     for (int j = 0; j < 16; ++j) {
-                        double &dst = lu[t.tail_base + tail_at(M, 16 * I + i, 16 * J + j)];
+                        double &dst = a[16 * I + i][16 * J + j];
                         double acc = dst;
                         for (int ks = 0; ks < KS; ++ks)
                             for (int kk = 0; kk < 4; ++kk)
@@ -167,9 +179,6 @@ int emulate_cell(const HostTables &t, const double *k, const double *y_species, 
 
     // dense tail: row r of the Schur complement, pivot rows broadcast
     if (M > 0) {
-        std::vector<std::vector<double>> a(M, std::vector<double>(M));
-        for (int r = 0; r < M; ++r)
-            for (int c = 0; c < M; ++c) a[r][c] = lu[t.tail_base + tail_at(M, r, c)];
         for (int kk = 0; kk < M; ++kk) {
             const double inv = 1.0 / a[kk][kk];
             for (int r = kk + 1; r < M; ++r) {
@@ -180,7 +189,7 @@ int emulate_cell(const HostTables &t, const double *k, const double *y_species, 
             a[kk][kk] = inv;
         }
         for (int r = 0; r < M; ++r)
-            for (int c = 0; c < M; ++c) lu[t.tail_base + tail_at(M, r, c)] = a[r][c];
+            for (int c = 0; c < M && !regs; ++c) lu[t.tail_base + tail_at(M, r, c)] = a[r][c];
     }
 
     // triangular sweeps in elimination order over virtual columns; a column
@@ -190,7 +199,14 @@ int emulate_cell(const HostTables &t, const double *k, const double *y_species, 
     for (int v = 0; v < NV; ++v)
         if (t.vspecies[v] >= 0) bv[v] = b_species[t.vspecies[v]];
     auto map_at = [&](const std::vector<uint16_t> &m, int u, int v) {
-        return (int)chk(m[(size_t)u * NV + v], t.lu_nnz + 2);
+        return (int)chk(m[(size_t)u * NV + v], t.lu_cells + 2);
+    };
+    // entry of the sweeps' L (forward) or U and 1/U_kk (backward)
+    auto factor = [&](bool fwd, int u, int v) {
+        const int o = map_at(fwd ? t.fwd_map : t.bwd_map, u, v);
+        if (!regs || u >= kWave || v >= kWave) return lu[o];
+        if (o != ZERO) bad++;
+        return (fwd ? u > v : u <= v) ? a[u][v] : 0.0;
     };
     for (int pk = 0; pk < N; ++pk) {
         const int v = t.vpos[pk], ks = v / kWave;
@@ -198,20 +214,20 @@ int emulate_cell(const HostTables &t, const double *k, const double *y_species, 
         for (int u = 0; u < NV; ++u) {
             const int o = map_at(t.fwd_map, u, v);
             if (ord(u / kWave) >= ord(ks))
-                bv[u] -= lu[o] * xk;
+                bv[u] -= factor(true, u, v) * xk;
             else if (o != ZERO)
                 bad++;  // an entry the kernel would skip
         }
     }
     for (int pk = N - 1; pk >= 0; --pk) {
         const int v = t.vpos[pk], ks = v / kWave;
-        const double xk = bv[v] * lu[map_at(t.bwd_map, v, v)];
+        const double xk = bv[v] * factor(false, v, v);
         for (int u = 0; u < NV; ++u) {
             const int o = map_at(t.bwd_map, u, v);
             if (u == v)
                 bv[u] = xk;
             else if (ord(u / kWave) <= ord(ks))
-                bv[u] -= lu[o] * xk;
+                bv[u] -= factor(false, u, v) * xk;
             else if (o != ZERO)
                 bad++;
         }

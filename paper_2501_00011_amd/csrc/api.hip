@@ -208,7 +208,7 @@ mcc_status mcc_mech_create_ex(const mcc_mech_desc *desc, int device, const mcc_m
     m->off_r = m->off_k + t.R;
     m->off_p = m->off_r;
     m->off_tm = m->off_r;
-    m->off_lu = m->off_r + std::max({t.R + 1, t.n_partials + 1, kTm, tail_panel_doubles(t.M)});
+    m->off_lu = m->off_r + std::max({t.R + 1, t.n_partials + 1, kTm, tail_panel_doubles(t.M, false)});
     m->lds_doubles = m->off_lu + t.lu_cells + 2;
     {
         // reverse mode: the same regions for the transposed tables, then R + 1 scratch values
@@ -218,7 +218,7 @@ mcc_status mcc_mech_create_ex(const mcc_mech_desc *desc, int device, const mcc_m
         d.off_k = a.N + 1;
         d.off_r = d.off_k + a.R;
         d.off_tm = d.off_r;
-        d.off_lu = d.off_r + std::max({a.R + 1, a.n_partials + 1, kTm, tail_panel_doubles(a.M)});
+        d.off_lu = d.off_r + std::max({a.R + 1, a.n_partials + 1, kTm, tail_panel_doubles(a.M, true)});
         // the R + 1 scratch values of the start entry, the last one reversed:
         // no factorisation follows, so they may take the LU storage
         d.off_w = a.lu_cells + 2 >= a.R + 1 ? d.off_lu : d.off_lu + a.lu_cells + 2;

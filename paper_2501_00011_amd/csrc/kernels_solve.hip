@@ -15,15 +15,17 @@
 //   registers : every per-species vector at virtual index v = s*64 + lane,
 //               s = 0..NS-1 (the mechanism compiler maps species to v): the
 //               backward differences D[0..7], the Newton correction, ...;
-//               during the factorisation also the dense tail of the LU
-//               (lane = row).
+//               from the factorisation on also the factors of the dense
+//               tail of the LU (lane = row; the reverse-mode kernel with a
+//               tail of 32 or 48 rows keeps them in LDS).
 //   LDS       : the evaluation point y, compact (slot s, lane l at the
 //               lanes in use of the earlier slots + l; then the constant 1),
 //               the cell's rate constants, one scratch region for the
 //               reaction rates, the rate partials or the 6 x 6 transform of a
-//               step-size change (never live together), and the LU factors
-//               (1/U_kk in place of U_kk; the tail block column-major; + a
-//               zero cell and a write-only cell).
+//               step-size change (never live together; then the tail's
+//               panels), and the LU factors (1/U_kk in place of U_kk; of the
+//               tail its Jacobian entries; + a zero cell and a write-only
+//               cell).
 //   HBM       : y in/out, k in, status and stats out; in the per-launch form
 //               the solver state between launches; when taping, the step
 //               tape.
@@ -220,16 +222,15 @@ __device__ __forceinline__ void static_for(F &&f)
     static_for_impl(std::make_integer_sequence<int, N>{}, f);
 }
 
-template <int NS, int M>
+// REGS: the dense tail in registers
+template <int NS, int M, bool REGS = tail_in_registers(M, false)>
 struct Cell {
     const SolveParams &p;
     double *yv, *kv, *rv, *pv, *lu, *tm;
     int lane;
     int N;
     bool vld[NS];
-    static constexpr bool kRegs = tail_in_registers(M);
-    static_assert(!kRegs || M == kWave, "a row of the tail in registers per lane");
-    double S[kRegs ? M : 1];  // kRegs: this lane's row of the tail's factors, 1/U_kk on the diagonal
+    double S[REGS ? M : 1];  // REGS: this lane's row of the tail's factors, 1/U_kk on the diagonal
 
     __device__ Cell(const SolveParams &pp, double *smem)
         : p(pp), yv(smem + pp.off_y), kv(smem + pp.off_k), rv(smem + pp.off_r), pv(smem + pp.off_p),
@@ -454,7 +455,7 @@ struct Cell {
         }
         const bool front_bad = __any(bad);
         bool tail_bad;
-        if constexpr (kRegs) {
+        if constexpr (REGS) {
             tail_bad = register_tail();
         } else {
             schur();
@@ -630,8 +631,8 @@ struct Cell {
     }
 
     // Schur complement and dense tail without the tail block in local memory
-    // (32 KB of a cell's 79 KB for 150 species, which let two cells run on a
-    // compute unit): the matrix-core accumulators start from the staged Jacobian
+    // (with 64 rows 32 KB of a cell's 79 KB for 150 species, which let two cells
+    // run on a compute unit): the matrix-core accumulators start from the staged Jacobian
     // entries, take all k-steps (each brings NT blocks of L and of U for its
     // NT x NT products) and stay in registers as the trailing matrix of the
     // blocked LU of dense_tail.  Per panel only its four columns and four rows
@@ -639,10 +640,12 @@ struct Cell {
     // (rows above the panel: U, which the accumulators took up from the row
     // phase), and each lane keeps its row of it in S, where the triangular
     // solves read it.   The same
-    // bits as with the block in local memory; one attempt of 150 species 155
-    // -> 128 us and three cells a compute unit instead of two (1,000 cells 281
-    // -> 214 ms), of 110 species 65 -> 52 us and eight instead of three (108 ->
-    // 63 ms).
+    // bits as with the block in local memory.  64 rows, one attempt of 150
+    // species 155 -> 128 us and three cells a compute unit instead of two (1,000
+    // cells 281 -> 214 ms), of 110 species 65 -> 52 us and eight instead of
+    // three (108 -> 63 ms); 48 rows, 72 species, 39 -> 32 us and eight instead
+    // of six (1,003 cells 38.5 -> 30.5 ms, 10,000 cells 195 -> 130); 32 rows, 72
+    // species, 8 cells 26.9 -> 25.3 ms, 10,000 cells 161 -> 139.
     __device__ __forceinline__ bool register_tail()
     {
         KParams &p = params_here();
@@ -653,13 +656,14 @@ struct Cell {
         {
             const uint4 *map = reinterpret_cast<const uint4 *>(p.tail_map) + lane;
 #pragma unroll
-            for (int v = 0; v < NT * NT / 2; ++v) {  // two tiles a vector of eight
+            for (int v = 0; v < (NT * NT + 1) / 2; ++v) {  // two tiles a vector of eight
                 const uint4 o = map[v * kWave];
                 const uint32_t w[4] = {o.x, o.y, o.z, o.w};
                 double x[8];
                 lds_fields8(w, lub, x);
 #pragma unroll
-                for (int e = 0; e < 8; ++e) acc[(2 * v + e / 4) / NT][(2 * v + e / 4) % NT][e % 4] = x[e];
+                for (int e = 0; e < 8; ++e)
+                    if (2 * v + e / 4 < NT * NT) acc[(2 * v + e / 4) / NT][(2 * v + e / 4) % NT][e % 4] = x[e];
             }
         }
         {
@@ -698,6 +702,8 @@ struct Cell {
             }
         }
         constexpr int ST = M + 4;
+        const bool in = lane < M;
+        const int row = in ? lane : 0;
         double *cb = rv, *rb = rv + 4 * ST;  // the panel's columns, [column][row]; its rows, [row][column]
         int bad = 0;
         static_for<M / 4>([&](auto PP) {
@@ -714,7 +720,7 @@ struct Cell {
             // panel: lane = row
             double a[4];
 #pragma unroll
-            for (int c = 0; c < 4; ++c) a[c] = cb[c * ST + lane];
+            for (int c = 0; c < 4; ++c) a[c] = cb[c * ST + row];
 #pragma unroll
             for (int kk = 0; kk < 4; ++kk) {
                 const int k = k0 + kk;
@@ -734,10 +740,11 @@ struct Cell {
             if constexpr (kt < M) {
                 lds_handover();
 #pragma unroll
-                for (int c = 0; c < 4; ++c) cb[c * ST + lane] = a[c];
+                for (int c = 0; c < 4; ++c)
+                    if (in) cb[c * ST + lane] = a[c];
                 lds_handover();
                 // the panel's rows right of it (unit lower L11): lane = column
-                if (lane >= kt) {
+                if (lane >= kt && in) {
                     const double l10 = cb[k0 + 1], l20 = cb[k0 + 2], l30 = cb[k0 + 3];
                     const double l21 = cb[ST + k0 + 2], l31 = cb[ST + k0 + 3], l32 = cb[2 * ST + k0 + 3];
                     const double u0 = rb[lane];
@@ -758,11 +765,11 @@ struct Cell {
                 double af[NT], bf[NT];
 #pragma unroll
                 for (int q = t1; q < NT; ++q) {
-                    const bool in = 16 * q + c16 >= kt;
+                    const bool right = 16 * q + c16 >= kt;
                     const double x = cb[g * ST + 16 * q + c16], y = rb[g * ST + 16 * q + c16];
-                    af[q] = in ? -x : 0.0;  // L(row, k0 + g)
-                    bf[q] = in ? y : 0.0;   // U(k0 + g, column)
-                    acc[t0][q][r0] = in ? y : acc[t0][q][r0];
+                    af[q] = right ? -x : 0.0;  // L(row, k0 + g)
+                    bf[q] = right ? y : 0.0;   // U(k0 + g, column)
+                    acc[t0][q][r0] = right ? y : acc[t0][q][r0];
                 }
 #pragma unroll
                 for (int i = t1; i < NT; ++i)
@@ -808,7 +815,7 @@ struct Cell {
                 for (int k8 = 0; k8 < M; k8 += 8) {
                     double tv[8];
 #pragma unroll
-                    for (int i = 0; i < 8; ++i) tv[i] = kRegs ? S[kRegs ? k8 + i : 0] : T[tat(trow, k8 + i)];
+                    for (int i = 0; i < 8; ++i) tv[i] = REGS ? S[REGS ? k8 + i : 0] : T[tat(trow, k8 + i)];
                     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                     for (int i = 0; i < 8; ++i) {
@@ -877,7 +884,7 @@ struct Cell {
                         for (int s = 1; s < NS; ++s) nxt[s] = bw[(size_t)(s * kWave + lane) * NVB + blk - 1];
                     double tv[8];  // 1/U_kk on the diagonal, U above it; loaded ahead as above
 #pragma unroll
-                    for (int i = 0; i < 8; ++i) tv[i] = kRegs ? S[kRegs ? blk * 8 + i : 0] : T[tat(trow, blk * 8 + i)];
+                    for (int i = 0; i < 8; ++i) tv[i] = REGS ? S[REGS ? blk * 8 + i : 0] : T[tat(trow, blk * 8 + i)];
                     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                     for (int i = 7; i >= 0; --i) {
@@ -1065,9 +1072,9 @@ struct GridSums<true> {
 // Wavefronts per SIMD the solver, reverse-mode and replay kernels are
 // compiled for: two for one or two register slots (up to 128 species) with a
 // dense tail of at most 48 rows, where the second wavefront hides more
-// latency than the few registers it spills cost (measured: 387 -> 295 ms for
-// 10,000 cells of 72 species); one for the larger shapes, whose registers
-// would spill heavily.
+// latency than the few registers it spills cost (72 species, tail of 48,
+// 10,000 cells: 214 -> 130 ms; 8 cells 23.9 -> 22.7 ms); one for the larger
+// shapes, whose registers would spill heavily.
 template <int NS, int M>
 constexpr int kSolveWaves = (NS <= 2 && M <= 48) ? 2 : 1;
 
@@ -1481,7 +1488,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kAdjointWave
     extern __shared__ double smem[];
     if ((int64_t)blockIdx.x >= p.n_cells) return;
     const int64_t cell = p.order ? p.order[blockIdx.x] : blockIdx.x;  // the batch's cell schedule
-    Cell<NS, M> C(p, smem);
+    Cell<NS, M, tail_in_registers(M, true)> C(p, smem);
     double *wv = smem + a.off_w;
     const int lane = C.lane, N = p.N;
     for (int j = lane; j < p.R; j += kWave) C.kv[j] = p.k[(int64_t)j * p.ld + cell];

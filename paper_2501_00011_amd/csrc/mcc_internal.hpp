@@ -26,12 +26,15 @@ __host__ __device__ constexpr int tail_at(int M, int row, int col)
 {
     return col * M + (row ^ (4 * (col & tail_swizzle_mask(M))));
 }
-// Whether the solver holds the dense tail in registers instead (see
-// Cell::factor in kernels_solve.hip); local memory then stages only the
-// tail's Jacobian entries, and two buffers for a panel of four columns and of
-// four rows (each M + 4 apart).
-constexpr bool tail_in_registers(int M) { return M == 64; }
-constexpr int tail_panel_doubles(int M) { return tail_in_registers(M) ? 8 * (M + 4) : 0; }
+// Whether the solver (the reverse-mode kernel, on the transposed tables) holds
+// the dense tail in registers instead (Cell::register_tail in
+// kernels_solve.hip); local memory then stages only the tail's Jacobian
+// entries, and two buffers for a panel of four columns and of four rows (each
+// M + 4 apart).  The reverse-mode kernel, which also holds its multipliers,
+// would no longer fit two wavefronts on a SIMD with a tail of 32 or 48 rows
+// (72 species, tail of 32, 4,000 cells: 45 -> 72 ms).
+constexpr bool tail_in_registers(int M, bool transposed) { return transposed ? M == 64 : M > 0; }
+constexpr int tail_panel_doubles(int M, bool transposed) { return tail_in_registers(M, transposed) ? 8 * (M + 4) : 0; }
 constexpr int kOffBits = 14;  // bits of an LDS offset inside an op
 constexpr uint32_t kOffMask = (1u << kOffBits) - 1;
 // flags of a Newton-matrix op (Op16::flags)

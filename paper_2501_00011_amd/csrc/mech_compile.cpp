@@ -518,7 +518,7 @@ mcc_status compile_mechanism(const mcc_mech_desc *d, int dense_tail, HostTables 
             if (lp[i][j] && !(i >= F && j >= F)) lpos[i][j] = nlu++;
     t->tail_base = nlu;
     t->lu_nnz = nlu + M * M;
-    if (tail_in_registers(M)) {  // the Jacobian's entries and the diagonal, staged
+    if (tail_in_registers(M, transpose)) {  // the Jacobian's entries and the diagonal, staged
         for (int i = F; i < N; ++i)
             for (int j = F; j < N; ++j)
                 if (i == j || spat[t->perm[i]][t->perm[j]]) lpos[i][j] = nlu++;
@@ -710,7 +710,7 @@ mcc_status compile_mechanism(const mcc_mech_desc *d, int dense_tail, HostTables 
     }
 
     t->tail_map.clear();
-    if (tail_in_registers(M)) {
+    if (tail_in_registers(M, transpose)) {
         const int nt = M / 16, n_map = (4 * nt * nt + 7) / 8 * 8;
         t->tail_map.assign((size_t)n_map * kWave, (uint16_t)ZERO);
         for (int lane = 0; lane < kWave; ++lane)
@@ -730,7 +730,7 @@ mcc_status compile_mechanism(const mcc_mech_desc *d, int dense_tail, HostTables 
     for (int pr = 0; pr < N; ++pr)
         for (int k = 0; k < N; ++k) {
             const size_t at = (size_t)vpos[pr] * t->NV + vpos[k];
-            if (tail_in_registers(M) && pr >= F && k >= F) continue;
+            if (tail_in_registers(M, transpose) && pr >= F && k >= F) continue;
             if (pr > k && lp[pr][k]) t->fwd_map[at] = (uint16_t)lpos[pr][k];
             if (pr <= k && lp[pr][k]) t->bwd_map[at] = (uint16_t)lpos[pr][k];
         }

@@ -139,9 +139,9 @@ int emulate_cell(const HostTables &t, const double *k, const double *y_species, 
 
     // The tail block, from its places in the LU storage or from its staged
     // entries (each read where the map says, the others zero).
-    const bool regs = tail_in_registers(M);
+    const bool regs = tail_in_registers(M, t.transposed);
     std::vector<std::vector<double>> a(M, std::vector<double>(M));
-    if (regs && t.tail_map.size() != (size_t)M * M) bad++;
+    if (regs && t.tail_map.size() != (size_t)(M * M / kWave + 7) / 8 * 8 * kWave) bad++;
     for (int r = 0; r < M; ++r)
         for (int q = 0; q < M; ++q) {
             const int e = 4 * (r / 16 * (M / 16) + q / 16) + r % 16 / 4, lane = 16 * (r % 4) + q % 16;
@@ -206,7 +206,7 @@ int emulate_cell(const HostTables &t, const double *k, const double *y_species, 
         const int o = map_at(fwd ? t.fwd_map : t.bwd_map, u, v);
         if (!regs || u >= kWave || v >= kWave) return lu[o];
         if (o != ZERO) bad++;
-        return (fwd ? u > v : u <= v) ? a[u][v] : 0.0;
+        return u < M && (fwd ? u > v : u <= v) ? a[u][v] : 0.0;
     };
     for (int pk = 0; pk < N; ++pk) {
         const int v = t.vpos[pk], ks = v / kWave;

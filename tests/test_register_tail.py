@@ -9,7 +9,8 @@ import pytest
 import tape_format
 from paper_2501_00011_amd import mcchem, synth
 
-SHAPES = [(64, 64), (65, 64), (68, 64), (69, 64), (80, 64), (81, 64), (129, 64)]
+SHAPES = [(32, 32), (33, 32), (36, 32), (49, 32), (96, 32), (48, 48), (49, 48), (64, 48), (65, 48), (112, 48),
+          (64, 64), (65, 64), (68, 64), (69, 64), (80, 64), (81, 64), (129, 64)]
 
 
 @pytest.mark.parametrize("n,tail", SHAPES)

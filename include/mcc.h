@@ -173,10 +173,13 @@ mcc_status mcc_mech_create(const mcc_mech_desc *desc, int device, mcc_mech **out
  * one wavefront (more registers, fewer cells per compute unit; built for
  * every shape), 2 two wavefronts (only where that is the library's choice;
  * MCC_ERR_INVALID_ARG otherwise).  Results are identical bit for bit.
- * (Mechanisms integrated four cells to a wavefront -- at most 32 species and
- * 128 reactions with dense_tail 0, or at most 96 species and 256 reactions
- * with dense_tail 32 -- have one build of mcc_solve_step and of its taped and
- * per-launch forms, which serves either value.)
+ * (Batches integrated four cells to a wavefront -- at most 32 species and 128
+ * reactions with dense_tail 0; or more than eight cells per compute unit of a
+ * mechanism of at most 96 species and 256 reactions with dense_tail 32, where
+ * 12 cells fit a compute unit's local memory -- have one build of
+ * mcc_solve_step and of its taped and per-launch forms, which serves either
+ * value.  With dense_tail 32 the results of such a batch and of a smaller one
+ * agree within rounding, not bit for bit.)
  * reserved: zero. */
 typedef struct {
     int32_t dense_tail;

@@ -34,6 +34,7 @@ struct mcc_mech {
     const uint16_t *schur_tab = nullptr, *tail_map = nullptr;
     int32_t off_y = 0, off_k = 0, off_r = 0, off_p = 0, off_lu = 0, off_tm = 0, lds_doubles = 0;
     QuadParams quad{};  // the quad solver's tables and sizes (t.quad.ok)
+    int n_cu = 0;  // compute units of the device
     int live_batches = 0;
     int solve_waves = 0;  // wavefronts per SIMD of the solver build launched
     // mechanism-specialised f/J kernel, compiled on first use
@@ -257,6 +258,7 @@ mcc_status mcc_mech_create_ex(const mcc_mech_desc *desc, int device, const mcc_m
             return hip_error(e, "hipGetDeviceProperties");
         }
         m->arch = prop.gcnArchName;
+        m->n_cu = prop.multiProcessorCount;
     }
     // Device limits (Section 3: checked at run time rather than assumed).
     int max_lds = 0;
@@ -1042,10 +1044,24 @@ static QuadParams quad_params(const mcc_mech *m, const SolveParams &p)
     return q;
 }
 
-// One launch of the outer step on the kernel that takes the mechanism's shape.
+// Whether the four-cells-per-wavefront kernels take a batch.  Without a front
+// they are faster at any size (32 species: 8 cells 14.0 -> 9.7 ms, 10,000
+// cells 68 -> 33 ms).  With one, a row's chain is longer than that of the
+// wavefront that a cell has to itself in the one-cell kernels, which hold
+// eight cells on a compute unit: the four-cells kernels take what is more than
+// these hold at once.  (Tail of 32, one cell / four cells a wavefront: 36
+// species, 2,048 cells 14.4 / 16.3 ms, 4,000 cells 22.2 / 17.1; 72 species,
+// 151 reactions, 1,003 cells 39 / 47 ms, 2,048 cells 43 / 47, 4,000 cells 73 /
+// 50, 10,000 cells 146 / 111.)
+static bool takes_quad(const mcc_mech *m, int64_t n_cells)
+{
+    return m->t.quad.ok && (m->t.quad.FB == 0 || n_cells > 8 * (int64_t)m->n_cu);
+}
+
+// One launch of the outer step on the kernel that takes the batch.
 static hipError_t launch_outer_step(const mcc_mech *m, const SolveParams &p, hipStream_t s)
 {
-    if (!m->t.quad.ok) return launch_solve(p, m->t.NS, m->t.M, p.tape ? 0 : m->solve_waves, s);
+    if (!takes_quad(m, p.n_cells)) return launch_solve(p, m->t.NS, m->t.M, p.tape ? 0 : m->solve_waves, s);
     return launch_quad(m->t.quad, quad_params(m, p), s);
 }
 
@@ -1080,7 +1096,7 @@ static mcc_status solve_step(mcc_cells *c, double *y, double dt, const mcc_solve
     // Per-launch form: state in HBM between launches; relaunch until every
     // cell has finished.  Every launch takes each unfinished cell at least one
     // accepted step (or to its end), so max_steps / K + 1 launches suffice.
-    p.state_stride = (int64_t)(kMaxOrder + 3) * (m->t.quad.ok ? m->t.quad.NB * kQLanes : m->t.NV) + kStateScalars;
+    p.state_stride = (int64_t)(kMaxOrder + 3) * (takes_quad(m, c->n_cells) ? m->t.quad.NB * kQLanes : m->t.NV) + kStateScalars;
     const int64_t need = p.state_stride * c->n_cells;
     hipStream_t s = (hipStream_t)stream;
     if (c->state_doubles < need) {

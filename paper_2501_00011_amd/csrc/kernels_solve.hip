@@ -727,13 +727,12 @@ struct Cell {
                 const double ukk = lane_bcast(a[kk], k);
                 bad |= !(fabs(ukk) >= 1e-300) || !isfinite(ukk);
                 const double inv = pivot_rcp(ukk);
-                if (lane > k) {
-                    const double l = a[kk] * inv;
-                    a[kk] = l;
+                // (selects, no branches: the compiler can then place the last
+                // panel's products between these dependent steps)
+                const double l = a[kk] * inv, l0 = lane > k ? l : 0.0;
+                a[kk] = lane > k ? l : (lane == k ? inv : a[kk]);
 #pragma unroll
-                    for (int c = kk + 1; c < 4; ++c) a[c] -= l * lane_bcast(a[c], k);
-                }
-                if (lane == k) a[kk] = inv;
+                for (int c = kk + 1; c < 4; ++c) a[c] -= l0 * lane_bcast(a[c], k);
             }
 #pragma unroll
             for (int c = 0; c < 4; ++c) S[k0 + c] = a[c];
@@ -741,23 +740,23 @@ struct Cell {
                 lds_handover();
 #pragma unroll
                 for (int c = 0; c < 4; ++c)
-                    if (in) cb[c * ST + lane] = a[c];
+                    if (M == kWave || in) cb[c * ST + row] = a[c];
                 lds_handover();
                 // the panel's rows right of it (unit lower L11): lane = column
-                if (lane >= kt && in) {
+                {  // (columns left of kt get values that nothing reads)
                     const double l10 = cb[k0 + 1], l20 = cb[k0 + 2], l30 = cb[k0 + 3];
                     const double l21 = cb[ST + k0 + 2], l31 = cb[ST + k0 + 3], l32 = cb[2 * ST + k0 + 3];
-                    const double u0 = rb[lane];
-                    double u1 = rb[ST + lane], u2 = rb[2 * ST + lane], u3 = rb[3 * ST + lane];
+                    const double u0 = rb[row];
+                    double u1 = rb[ST + row], u2 = rb[2 * ST + row], u3 = rb[3 * ST + row];
                     u1 -= l10 * u0;
                     u2 -= l20 * u0;
                     u2 -= l21 * u1;
                     u3 -= l30 * u0;
                     u3 -= l31 * u1;
                     u3 -= l32 * u2;
-                    rb[ST + lane] = u1;
-                    rb[2 * ST + lane] = u2;
-                    rb[3 * ST + lane] = u3;
+                    rb[ST + row] = u1;
+                    rb[2 * ST + row] = u2;
+                    rb[3 * ST + row] = u3;
                 }
                 lds_handover();
                 // trailing update on the tiles that meet rows and columns >= kt

@@ -613,6 +613,7 @@ mcc_status mcc_cells_rate_constants(const mcc_cells *c, const double **k)
 
 // Memory-side cache of the MI355X (Infinity Cache), bytes.
 constexpr int64_t kMallBytes = (int64_t)256 << 20;
+constexpr int kGeneratedArrays = 5;  // at most, of a generated kernel
 
 // Launches a generated kernel over cells [0, n_cells).  arrays: the kernel's
 // pointer arguments in order (null allowed for an unused output).  in_rows:
@@ -637,11 +638,12 @@ constexpr int64_t kMallBytes = (int64_t)256 << 20;
 //   are long runs (200,000 cells: 409 us, 128 tiles of 64 lanes 413, 64 lanes
 //   without groups 505); the VJP kernel, mostly reads, as within the cache
 //   (its items reuse the XCD's L2).
-static mcc_status launch_generated(hipFunction_t fn, hipFunction_t fn2, std::vector<const void *> arrays,
+static mcc_status launch_generated(hipFunction_t fn, hipFunction_t fn2, std::initializer_list<const void *> arrays,
                                    int64_t n_cells, int64_t ld, int item_begin, int n_items, int in_rows,
                                    bool streams, void *stream)
 {
     if (n_items == 0 || n_cells == 0) return ok();
+    if (arrays.size() > kGeneratedArrays) return set_error(MCC_ERR_INVALID_ARG, "too many arrays");
     const bool pair = n_cells > 8 * kWave, odd = ld % 2 != 0;
     const int64_t lanes = pair ? (n_cells + 1) / 2 : n_cells;
     const bool groups = !odd && streams && 8 * (int64_t)in_rows * n_cells > kMallBytes;
@@ -650,13 +652,15 @@ static mcc_status launch_generated(hipFunction_t fn, hipFunction_t fn2, std::vec
     const int grp = groups ? (int)std::min<int64_t>(4, (n_tiles + 7) / 8) : 1;
     const int64_t blocks = (n_tiles + 8 * grp - 1) / (8 * grp) * 8 * grp * n_items;
     if (blocks > 0x7fffffff) return set_error(MCC_ERR_INVALID_ARG, "too many cells for one launch");
-    std::vector<void *> args;
-    for (const void *&a : arrays) args.push_back((void *)&a);
     long long nc = n_cells, ldl = ld;
-    int ib = item_begin, ni = n_items, nt = (int)n_tiles, gt = grp;
-    for (void *a : {(void *)&nc, (void *)&ldl, (void *)&ib, (void *)&ni, (void *)&nt, (void *)&gt}) args.push_back(a);
+    int ib = item_begin, ni = n_items, nt = (int)n_tiles, gt = grp, tl = threads;
+    void *args[kGeneratedArrays + 7];
+    int n_args = 0;
+    for (const void *const &a : arrays) args[n_args++] = (void *)&a;
+    for (void *a : {(void *)&nc, (void *)&ldl, (void *)&ib, (void *)&ni, (void *)&nt, (void *)&gt, (void *)&tl})
+        args[n_args++] = a;
     const hipError_t e = hipModuleLaunchKernel(pair ? fn2 : fn, (unsigned)blocks, 1, 1, (unsigned)threads, 1, 1, 0,
-                                               (hipStream_t)stream, args.data(), nullptr);
+                                               (hipStream_t)stream, args, nullptr);
     if (e != hipSuccess) return hip_error(e, "generated kernel launch");
     return ok();
 }

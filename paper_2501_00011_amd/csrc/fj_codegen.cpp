@@ -50,7 +50,7 @@ std::string fill(std::string s, bool pair)
     return s;
 }
 
-// Kernel head: block -> (tile of blockDim.x lanes, work item).  Blocks come
+// Kernel head: block -> (tile of `lanes` lanes, work item).  Blocks come
 // in groups of 8 * grp_tiles tiles times n_items; within a group the order is
 // item major: block q of XCD xcd (bid = 8 q + xcd) runs item r / grp_tiles on
 // tile (group * grp_tiles + r % grp_tiles) * 8 + xcd, r = q mod (n_items *
@@ -59,26 +59,27 @@ std::string fill(std::string s, bool pair)
 // that XCD's L2); a larger grp_tiles runs each item over 8 * grp_tiles
 // consecutive tiles at about the same time, so that the first reads of every
 // row are long runs of consecutive cells.  One-cell variant: lane = cell
-// tile * blockDim.x + lane.  Pair variant: lane = cells c and c + 1 with
-// c = 2 (tile * blockDim.x + lane), 16-byte accesses that need 8-byte
+// tile * lanes + lane.  Pair variant: lane = cells c and c + 1 with
+// c = 2 (tile * lanes + lane), 16-byte accesses that need 8-byte
 // alignment only, so any leading dimension; the last pair of an odd n_cells
 // is shifted down by one cell, which two lanes then write with the same bits.
 std::string head(const char *name, const char *args, const char *ptrs, bool pair)
 {
     std::ostringstream o;
     o << "extern \"C\" __global__ __launch_bounds__(256) void " << name << (pair ? "2" : "") << "(\n" << args
-      << ", long long n_cells, long long ld, int item_begin, int n_items, int n_tiles, int grp_tiles)\n"
+      << ", long long n_cells, long long ld, int item_begin, int n_items, int n_tiles, int grp_tiles,\n"
+      << "    int lanes)\n"
       << "{\n"
       << "    const int bid = blockIdx.x, xcd = bid & 7, q = bid >> 3;\n"
       << "    const int grp = q / (n_items * grp_tiles), r = q - grp * (n_items * grp_tiles);\n"
       << "    const int item = item_begin + r / grp_tiles, tile = (grp * grp_tiles + r % grp_tiles) * 8 + xcd;\n"
       << "    if (tile >= n_tiles) return;\n";
     if (pair)
-        o << "    const long long c0 = 2 * ((long long)tile * blockDim.x + threadIdx.x), ldv = ld;\n"
+        o << "    const long long c0 = 2 * ((long long)tile * lanes + threadIdx.x), ldv = ld;\n"
           << "    if (c0 >= n_cells || n_cells < 2) return;\n"
           << "    const long long c = c0 + 1 < n_cells ? c0 : n_cells - 2;\n";
     else
-        o << "    const long long c = (long long)tile * blockDim.x + threadIdx.x;\n"
+        o << "    const long long c = (long long)tile * lanes + threadIdx.x;\n"
           << "    if (c >= n_cells) return;\n";
     o << ptrs;
     return o.str();

@@ -1097,17 +1097,15 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(W, W))) void
         C.kr[u] = j < p.R && live ? p.k[(int64_t)j * p.ld + cell] : 0.0;
     }
     int sp[NB];
-    // D[0..5] the backward differences; of the steps taken at this order and
-    // spacing: d1 the last Newton correction (the difference of order + 1), d2
-    // its change against the one before (of order + 2)
-    double D[KO + 1][NB], d1[NB], d2[NB], f[NB], w[NB], ypred[NB], psi[NB], d[NB], tmp[NB];
+    // D[0..5] the backward differences; d1 the last Newton correction at this
+    // order and spacing (the difference of order + 1)
+    double D[KO + 1][NB], d1[NB], f[NB], w[NB], ypred[NB], psi[NB], d[NB], tmp[NB];
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
         sp[b] = p.vsp[b * 16 + i];
 #pragma unroll
         for (int j = 0; j < KO + 1; ++j) D[j][b] = resumed && live ? st_d[(j * NB + b) * 16 + i] : 0.0;
         d1[b] = resumed && live ? st_d[((KO + 1) * NB + b) * 16 + i] : 0.0;
-        d2[b] = resumed && live ? st_d[((KO + 2) * NB + b) * 16 + i] : 0.0;
         if (!resumed && live && sp[b] >= 0) D[0][b] = p.y[(int64_t)sp[b] * p.ld + cell];
     }
     auto nonfinite = [&](const double (&v)[NB]) {
@@ -1390,6 +1388,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(W, W))) void
             steps_here++;
             n_equal++;
         }
+        double d2[NB];  // the correction's change against the one before (the difference of order + 2)
         {
             // D_j += D_{j+1} from the order down, the new difference of order + 1
             // being d; the factors are 1 or 0 (an attempt that was not accepted)
@@ -1405,7 +1404,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(W, W))) void
                     D[j][b] = fma(m[j], sum, old);
                     sum = fma(m[j], old, sum);
                 }
-                d2[b] = accept ? d[b] - d1[b] : d2[b];
+                d2[b] = d[b] - d1[b];
                 d1[b] = accept ? d[b] : d1[b];
             }
         }
@@ -1476,9 +1475,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(W, W))) void
 
     if (susp) {
 #pragma unroll
-        for (int j = 0; j < KO + 3; ++j)
+        for (int j = 0; j < KO + 2; ++j)
 #pragma unroll
-            for (int b = 0; b < NB; ++b) st_d[(j * NB + b) * 16 + i] = j <= KO ? D[j < KO ? j : KO][b] : (j == KO + 1 ? d1[b] : d2[b]);
+            for (int b = 0; b < NB; ++b) st_d[(j * NB + b) * 16 + i] = j <= KO ? D[j < KO ? j : KO][b] : d1[b];
         if (i == 0) {
             st_s[0] = (double)p.call_id;
             st_s[1] = 1.0;

@@ -653,11 +653,11 @@ static mcc_status launch_generated(hipFunction_t fn, hipFunction_t fn2, std::ini
     const int64_t blocks = (n_tiles + 8 * grp - 1) / (8 * grp) * 8 * grp * n_items;
     if (blocks > 0x7fffffff) return set_error(MCC_ERR_INVALID_ARG, "too many cells for one launch");
     long long nc = n_cells, ldl = ld;
-    int ib = item_begin, ni = n_items, nt = (int)n_tiles, gt = grp, tl = threads;
-    void *args[kGeneratedArrays + 7];
+    int ib = item_begin, ni = n_items, nt = (int)n_tiles, shape = threads << 16 | grp;
+    void *args[kGeneratedArrays + 6];
     int n_args = 0;
     for (const void *const &a : arrays) args[n_args++] = (void *)&a;
-    for (void *a : {(void *)&nc, (void *)&ldl, (void *)&ib, (void *)&ni, (void *)&nt, (void *)&gt, (void *)&tl})
+    for (void *a : {(void *)&nc, (void *)&ldl, (void *)&ib, (void *)&ni, (void *)&nt, (void *)&shape})
         args[n_args++] = a;
     const hipError_t e = hipModuleLaunchKernel(pair ? fn2 : fn, (unsigned)blocks, 1, 1, (unsigned)threads, 1, 1, 0,
                                                (hipStream_t)stream, args, nullptr);

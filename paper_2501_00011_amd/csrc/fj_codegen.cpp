@@ -67,9 +67,9 @@ std::string head(const char *name, const char *args, const char *ptrs, bool pair
 {
     std::ostringstream o;
     o << "extern \"C\" __global__ __launch_bounds__(256) void " << name << (pair ? "2" : "") << "(\n" << args
-      << ", long long n_cells, long long ld, int item_begin, int n_items, int n_tiles, int grp_tiles,\n"
-      << "    int lanes)\n"
+      << ", long long n_cells, long long ld, int item_begin, int n_items, int n_tiles, int shape)\n"
       << "{\n"
+      << "    const int grp_tiles = shape & 0xffff, lanes = shape >> 16;  // (one argument: all fit a cache line)\n"
       << "    const int bid = blockIdx.x, xcd = bid & 7, q = bid >> 3;\n"
       << "    const int grp = q / (n_items * grp_tiles), r = q - grp * (n_items * grp_tiles);\n"
       << "    const int item = item_begin + r / grp_tiles, tile = (grp * grp_tiles + r % grp_tiles) * 8 + xcd;\n"

@@ -30,8 +30,10 @@ FP64_VALU_PEAK_TFLOPS = 78.6  # MI355X FP64 vector
 VALU_ISSUE_PEAK = 256 * 4 * 2.4e9 / 4  # wavefront-instructions/s
 
 
-SOLVE_SOURCES = ["paper_2501_00011_amd/csrc/kernels_solve.hip", "paper_2501_00011_amd/csrc/mcc_internal.hpp",
-                 "paper_2501_00011_amd/csrc/mech_compile.cpp"]
+SOLVE_SOURCES = ["paper_2501_00011_amd/csrc/quad_kernel.hpp", "paper_2501_00011_amd/csrc/quad_tables.hpp",
+                 "paper_2501_00011_amd/csrc/quad_launch.hpp", "paper_2501_00011_amd/csrc/kernels_quad_front34.hip",
+                 "paper_2501_00011_amd/csrc/mcc_internal.hpp", "paper_2501_00011_amd/csrc/mech_compile.cpp"]
+SOLVE_KERNEL = "quad_kernel"  # the 72-species mechanism with the 32-row tail at 10,000 cells
 FJ_SOURCES = ["paper_2501_00011_amd/csrc/fj_codegen.cpp", "paper_2501_00011_amd/csrc/mcc_internal.hpp",
               "paper_2501_00011_amd/csrc/mech_compile.cpp", "paper_2501_00011_amd/csrc/api.hip"]
 FJ_KERNEL = "mcc_fj_generated2"  # the two-cell variant
@@ -65,9 +67,9 @@ def measured_traffic(kernel, sources, n_cells=10000):
 def solver_counter(key, n_cells, dense_tail):
     """A counter figure of the solver launch, only for the configuration it
     was measured in (10,000 cells, the recorded dense-tail size)."""
-    if n_cells != 10000 or measured_counter("bdf_kernel", SOLVE_SOURCES, "dense_tail") != dense_tail:
+    if n_cells != 10000 or measured_counter(SOLVE_KERNEL, SOLVE_SOURCES, "dense_tail") != dense_tail:
         return None
-    return measured_counter("bdf_kernel", SOLVE_SOURCES, key)
+    return measured_counter(SOLVE_KERNEL, SOLVE_SOURCES, key)
 
 
 def issue_roofline(launch_s, n_cells, dense_tail):
@@ -93,7 +95,7 @@ def per_launch_state(sn, K, n_species, mech):
         return None
     import numpy as np
     ns = len([b for b in mech.schedule_info()["fg_blocks"] if b > 0]) or 1
-    state_bytes = 8 * (8 * ns * 64 + 16)
+    state_bytes = 8 * (8 * ns * 64 + 24)
     launches = np.ceil(sn["steps"].astype(np.float64) / K)
     return {"state_bytes_per_cell": state_bytes, "launches_max": int(launches.max()),
             "bytes_per_outer_step": float(2 * state_bytes * np.maximum(launches - 1, 0).sum())}
@@ -302,7 +304,7 @@ def bench_mixed(args):
                                  f"graph (3 streams); one timed step = one replay",
                    "cells": C, "dt_s": dt, "window": W, "rtol": opts.rtol, "atol": opts.atol,
                    "cell_schedule": "per batch, longest first by the counters of an eager first step"},
-        "roofline": {"kernel": "bdf_kernel x 3 mechanisms (solve_step)", "bound": "alu", "achieved": tf,
+        "roofline": {"kernel": "quad_kernel and bdf_kernel, 3 mechanisms (solve_step)", "bound": "alu", "achieved": tf,
                      "peak": FP64_VALU_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": tf / FP64_VALU_PEAK_TFLOPS,
                      "traffic": None, "replay_ms": gpu_s / args.steps * 1e3, "flops_per_replay": flops / args.steps},
         "solver": {"failed_cells": failed},
@@ -809,7 +811,7 @@ def main():
                    "autotune_ms": {k: round(v, 2) for k, v in tuned.items()} if tuned else None,
                    "autotune_note": "keys: dense tail / wavefronts per SIMD / cell schedule; one outer step of "
                                     "the first 8,192 cells" if tuned else None},
-        "roofline": {"kernel": "bdf_kernel (solve_step)", "bound": "alu", "achieved": achieved_tf,
+        "roofline": {"kernel": "quad_kernel or bdf_kernel (solve_step)", "bound": "alu", "achieved": achieved_tf,
                      "peak": FP64_VALU_PEAK_TFLOPS, "unit": "TFLOP/s",
                      "frac": achieved_tf / FP64_VALU_PEAK_TFLOPS,
                      "traffic": solver_counter("traffic_bytes", C, tail_measured),

@@ -18,9 +18,9 @@
 // 72 species: 16 cells per compute unit, one wavefront per SIMD).
 //
 // Measured against the one-cell-per-wavefront kernel: 10,000 cells of 72
-// species, one 180 s step (cells longest first, 32-row tail) 156.2 -> 92.3 ms;
-// 30,000 cells of 20 species, 60 s 97.3 -> 34.3 ms; 10 cells of 20 species
-// 9.8 -> 6.3 ms.  A wavefront's step attempt takes 106,000 cycles for four
+// species, one 180 s step (cells longest first, 32-row tail) 156 -> 91 ms;
+// 30,000 cells of 20 species, 60 s 97 -> 33 ms; 10 cells of 20 species
+// 8.4 -> 5.5 ms.  A wavefront's step attempt takes 106,000 cycles for four
 // cells of 72 species (the other kernel: 105,000 for one, two sharing a SIMD):
 // 14,700 instructions at 4.4 cycles each, a wavefront alone on its SIMD
 // issuing at most one per four, and about 35,000 cycles of waits on dependent

@@ -174,12 +174,12 @@ mcc_status mcc_mech_create(const mcc_mech_desc *desc, int device, mcc_mech **out
  * every shape), 2 two wavefronts (only where that is the library's choice;
  * MCC_ERR_INVALID_ARG otherwise).  Results are identical bit for bit.
  * (Batches integrated four cells to a wavefront -- at most 32 species and 128
- * reactions with dense_tail 0; or more than eight cells per compute unit of a
- * mechanism of at most 96 species and 256 reactions with dense_tail 32, where
- * 12 cells fit a compute unit's local memory -- have one build of
- * mcc_solve_step and of its taped and per-launch forms, which serves either
- * value.  With dense_tail 32 the results of such a batch and of a smaller one
- * agree within rounding, not bit for bit.)
+ * reactions with dense_tail 0; or more than 8.5 cells per compute unit (ten up
+ * to 36 species) of a mechanism of at most 96 species and 256 reactions with
+ * dense_tail 32, where 12 cells fit a compute unit's local memory -- have one
+ * build of mcc_solve_step and of its taped and per-launch forms, which serves
+ * either value.  With dense_tail 32 the results of such a batch and of a
+ * smaller one agree within rounding, not bit for bit.)
  * reserved: zero. */
 typedef struct {
     int32_t dense_tail;
@@ -290,6 +290,15 @@ mcc_status mcc_debug_compile_fj(const mcc_mech *mech, const char *arch, int64_t 
  * the size of the dense tail, and the wavefronts per SIMD of the solver
  * build mcc_solve_step launches. */
 mcc_status mcc_debug_schedule_info(const mcc_mech *mech, int64_t *out);
+
+/* Testing aid (host only): which solver a batch of n_cells cells gets on a
+ * device with n_cu compute units (0: the mechanism's device; MCC_ERR_STATE for
+ * a host-only mechanism then).  out[0]: cells per wavefront of the kernel that
+ * mcc_solve_step and its taped and per-launch forms launch (1 or 4); out[1]:
+ * doubles of solver state per cell the per-launch form keeps between launches;
+ * out[2]: how many of them a launch that leaves the cell unfinished writes, and
+ * the next one reads. */
+mcc_status mcc_debug_solver_dispatch(const mcc_mech *mech, int64_t n_cells, int32_t n_cu, int64_t *out);
 
 /* Release a mechanism.  MCC_ERR_STATE if cell batches created from it are
  * still alive (nothing is released then). */

@@ -1052,14 +1052,44 @@ static QuadParams quad_params(const mcc_mech *m, const SolveParams &p)
 // they are faster at any size (32 species: 8 cells 14.0 -> 9.7 ms, 10,000
 // cells 68 -> 33 ms).  With one, a row's chain is longer than that of the
 // wavefront that a cell has to itself in the one-cell kernels, which hold
-// eight cells on a compute unit: the four-cells kernels take what is more than
-// these hold at once.  (Tail of 32, one cell / four cells a wavefront: 36
-// species, 2,048 cells 14.4 / 16.3 ms, 4,000 cells 22.2 / 17.1; 72 species,
-// 151 reactions, 1,003 cells 39 / 47 ms, 2,048 cells 43 / 47, 4,000 cells 73 /
-// 50, 10,000 cells 146 / 111.)
-static bool takes_quad(const mcc_mech *m, int64_t n_cells)
+// eight cells on a compute unit and are faster until clearly more than these
+// wait for a place: half a cell a compute unit more, or two where the front
+// has at most four positions (a cell is then short work for a wavefront of its
+// own).  Tail of 32, 256 compute units, one cell / four cells a wavefront, ms:
+//                2,049        2,176        2,304        2,560        3,072 cells
+//   33 species   22.0 / 28.0  22.5 / 26.8  24.6 / 25.1  26.2 / 28.9  27.7 / 27.3
+//   36           20.3 / 25.2  23.2 / 26.0  24.3 / 27.7  24.7 / 24.4  29.3 / 26.0
+//   37           20.7 / 25.6  28.5 / 27.1  29.4 / 29.2  27.1 / 24.9  31.4 / 30.8
+//   40           25.7 / 27.6  28.5 / 27.9  31.6 / 28.6  35.2 / 30.2  35.2 / 32.4
+//   52           31.0 / 35.7  35.7 / 36.5  35.4 / 32.2  41.8 / 32.6  43.6 / 34.7
+//   72           37.2 / 39.6  46.3 / 41.0  49.9 / 38.7  48.9 / 41.0  54.5 / 41.0
+//   80           43.4 / 44.9  48.7 / 42.0  49.4 / 43.4  51.0 / 42.3  57.2 / 42.2
+static bool takes_quad(const mcc_mech *m, int64_t n_cells, int64_t n_cu)
 {
-    return m->t.quad.ok && (m->t.quad.FB == 0 || n_cells > 8 * (int64_t)m->n_cu);
+    if (!m->t.quad.ok) return false;
+    return m->t.quad.FB == 0 || 2 * n_cells > (m->t.quad.F <= 4 ? 20 : 17) * n_cu;
+}
+static bool takes_quad(const mcc_mech *m, int64_t n_cells) { return takes_quad(m, n_cells, m->n_cu); }
+
+// Doubles of solver state per cell that the per-launch form keeps between launches.
+static int64_t state_doubles(const mcc_mech *m, bool quad)
+{
+    return (int64_t)(kMaxOrder + 3) * (quad ? m->t.quad.NB * kQLanes : m->t.NV) + kStateScalars;
+}
+
+mcc_status mcc_debug_solver_dispatch(const mcc_mech *m, int64_t n_cells, int32_t n_cu, int64_t *out)
+{
+    if (!m || !out) return set_error(MCC_ERR_INVALID_ARG, "null argument");
+    if (n_cells < 0 || n_cells > 0x7fffffff || n_cu < 0) return set_error(MCC_ERR_INVALID_ARG, "n_cells or n_cu out of range");
+    if (n_cu == 0 && m->device < 0) return set_error(MCC_ERR_STATE, "mechanism was compiled host-only (device -1): give n_cu");
+    const bool quad = takes_quad(m, n_cells, n_cu ? n_cu : m->n_cu);
+    out[0] = quad ? kQCells : 1;
+    out[1] = state_doubles(m, quad);
+    // of it: the backward differences the kernel keeps (the four-cells kernels
+    // form the one of order + 2 afresh) and the scalars in use
+    out[2] = quad ? (int64_t)(kMaxOrder + 2) * m->t.quad.NB * kQLanes + kQuadStateScalars
+                  : (int64_t)(kMaxOrder + 3) * m->t.NV + kOneStateScalars;
+    return ok();
 }
 
 // One launch of the outer step on the kernel that takes the batch.
@@ -1100,7 +1130,7 @@ static mcc_status solve_step(mcc_cells *c, double *y, double dt, const mcc_solve
     // Per-launch form: state in HBM between launches; relaunch until every
     // cell has finished.  Every launch takes each unfinished cell at least one
     // accepted step (or to its end), so max_steps / K + 1 launches suffice.
-    p.state_stride = (int64_t)(kMaxOrder + 3) * (takes_quad(m, c->n_cells) ? m->t.quad.NB * kQLanes : m->t.NV) + kStateScalars;
+    p.state_stride = state_doubles(m, takes_quad(m, c->n_cells));
     const int64_t need = p.state_stride * c->n_cells;
     hipStream_t s = (hipStream_t)stream;
     if (c->state_doubles < need) {

@@ -367,6 +367,9 @@ struct SolveParams {
     int64_t tape_stride;
 };
 constexpr int kStateScalars = 24;
+// Those in use (without a tape): of bdf_kernel [0] .. [14], of the quad solver
+// [0] .. [11], [13], [14], [16] and [17].
+constexpr int kOneStateScalars = 15, kQuadStateScalars = 16;
 
 // Kernel parameters of the quad solver (kernels_quad.hip); the fields from
 // `order` on mean what they do in SolveParams.

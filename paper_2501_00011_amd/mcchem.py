@@ -74,6 +74,7 @@ def library(path: str = LIB_PATH) -> ctypes.CDLL:
         "mcc_mech_op_counts": ([vp, vp], ctypes.c_int),
         "mcc_debug_emulate_cell": ([vp, vp, vp, dbl, vp, vp, vp, vp], ctypes.c_int),
         "mcc_debug_schedule_info": ([vp, vp], ctypes.c_int),
+        "mcc_debug_solver_dispatch": ([vp, i64, i32, vp], ctypes.c_int),
         "mcc_debug_emulate_fj": ([vp, vp, vp, vp, vp, vp], ctypes.c_int),
         "mcc_debug_emulate_vjp": ([vp, vp, vp, vp, vp, vp, vp], ctypes.c_int),
         "mcc_debug_emulate_cell_adjoint": ([vp, vp, vp, dbl, vp, vp, vp, vp], ctypes.c_int),
@@ -263,6 +264,15 @@ class Mechanism:
         v = list(buf)
         return {"lu_blocks": v[0], "lu_levels": v[1], "nm_blocks": v[2], "fg_blocks": v[3:7],
                 "dense_tail": v[7], "waves_per_simd": v[8]}
+
+    def solver_dispatch(self, n_cells: int, n_cu: int = 0) -> dict:
+        """Which solver a batch of n_cells cells gets on a device with n_cu
+        compute units (0: this mechanism's device) (testing aid): cells per
+        wavefront, and the doubles of state per cell of the per-launch form,
+        kept and moved each way."""
+        buf = (ctypes.c_int64 * 3)()
+        _check(library().mcc_debug_solver_dispatch(self._h, int(n_cells), int(n_cu), ctypes.addressof(buf)))
+        return dict(zip(("cells_per_wavefront", "state_doubles", "state_moved"), list(buf)))
 
     def jac_pattern(self):
         rp = np.zeros(self.n_species + 1, dtype=np.int32)

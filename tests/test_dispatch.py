@@ -1,0 +1,41 @@
+"""Which kernel a batch gets (host logic, no GPU)."""
+import pytest
+
+from paper_2501_00011_amd import mcchem, synth
+
+
+def _cells_per_wavefront(h, n_cells, n_cu=256):
+    return h.solver_dispatch(n_cells, n_cu)["cells_per_wavefront"]
+
+
+@pytest.mark.parametrize("n,halves", [(33, 20), (36, 20), (37, 17), (48, 17), (49, 17), (72, 17)])
+@pytest.mark.parametrize("n_cu", [256, 64])
+def test_four_cells_with_a_front_only_beyond_what_the_one_cell_kernels_hold(n, halves, n_cu):
+    """`halves` half cells per compute unit: below that line the four-cells
+    kernels are the slower ones (2,049 cells of 33 to 40 species by 7 to 27 per
+    cent)."""
+    h = mcchem.Mechanism(synth.make_mechanism(n, 2 * n), device=-1, dense_tail=32)
+    line = halves * n_cu // 2
+    for cells in (1, 8 * n_cu, 8 * n_cu + 1, line):
+        assert _cells_per_wavefront(h, cells, n_cu) == 1, cells
+    for cells in (line + 1, 12 * n_cu, 100 * n_cu):
+        assert _cells_per_wavefront(h, cells, n_cu) == 4, cells
+
+
+def test_shapes_of_one_solver():
+    """Without a front (and without a tail) four cells a wavefront at any size;
+    shapes those kernels do not take, one cell."""
+    h = mcchem.Mechanism(synth.make_mechanism(20, 40), device=-1, dense_tail=0)
+    assert _cells_per_wavefront(h, 1) == _cells_per_wavefront(h, 100000) == 4
+    for n, r, tail in ((72, 144, 48), (72, 144, 0), (20, 129, 0), (96, 201, 32), (150, 350, 64)):
+        h = mcchem.Mechanism(synth.make_mechanism(n, r), device=-1, dense_tail=tail)
+        assert _cells_per_wavefront(h, 1) == _cells_per_wavefront(h, 100000) == 1
+
+
+def test_dispatch_arguments():
+    h = mcchem.Mechanism(synth.make_mechanism(20, 40), device=-1)
+    with pytest.raises(mcchem.MccError, match="status 5"):
+        h.solver_dispatch(10)
+    for cells, n_cu in ((-1, 256), (1 << 31, 256), (10, -1)):
+        with pytest.raises(mcchem.MccError, match="status 1"):
+            h.solver_dispatch(cells, n_cu)

@@ -1294,7 +1294,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(W, W))) void
             for (int j = 1; j <= KO; ++j) ps += (on[j] * bdf_gamma(j)) * D[j][b];
             ypred[b] = yp;
             psi[b] = ps * igk;
-            w[b] = sp[b] >= 0 ? pivot_rcp(o.rtol * fabs(D[0][b]) + o.atol) : 0.0;
+            // (the inverse of infinity would be NaN, by its Newton steps; 2^-1021 is zero once squared)
+            w[b] = sp[b] >= 0 ? pivot_rcp(fmin(o.rtol * fabs(D[0][b]) + o.atol, 0x1p1021)) : 0.0;
             d[b] = 0.0;
         }
         if (act) lu_count++;

@@ -160,3 +160,32 @@ def test_multicell(n, cells):
         st, stats = b.step(y, 20.0)
         assert torch.equal(y, out[0][0]) and torch.equal(stats, out[0][1])
     b.close()
+
+
+@pytest.mark.gpu
+def test_error_weights_beyond_the_range():
+    """rtol |y| beyond the largest double: a weight of zero, as in the oracle
+    and the one-cell kernels, and no NaN (tolerances this loose accept every
+    step, so both take the same ones)."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    oracle = pytest.importorskip("oracle")
+    dev = torch.device("cuda:0")
+    m = synth.make_mechanism(20, 40)
+    c = synth.make_cells(m, 5, seed=77)
+    y0 = np.maximum(c.y0, 1e9)
+    o = oracle.Oracle(m)
+    yo, so, sto = o.solve(o.rate_constants(c.T, c.jscale), y0, 60.0, oracle.default_opts(rtol=1e300))
+    assert np.all(so == 0)
+    h = mcchem.Mechanism(m, dense_tail=0)
+    b = mcchem.Cells(h, 5)
+    up = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(dev)  # noqa: E731
+    b.bind(up(c.T), up(c.P), up(c.jscale))
+    y = up(y0)
+    st, stats = b.step(y, 60.0, mcchem.default_opts(rtol=1e300))
+    torch.cuda.synchronize()
+    assert np.array_equal(st.cpu().numpy(), so)
+    assert np.array_equal(mcchem.stats_numpy(stats)["steps"], sto["steps"])
+    assert np.all(np.abs(y.cpu().numpy() - yo) <= 1e-6 * np.abs(yo) + 1e2)
+    b.close()

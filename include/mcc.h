@@ -285,6 +285,12 @@ mcc_status mcc_debug_fj_source(const mcc_mech *mech, char *buf, int64_t cap, int
  * compiler log in mcc_last_error() on failure. */
 mcc_status mcc_debug_compile_fj(const mcc_mech *mech, const char *arch, int64_t *code_bytes);
 
+/* Testing aid (host only): the shape of a generated kernel's launch over
+ * n_cells cells with leading dimension ld; kind 0 f, 1 J, 2 f and J, 3 VJP.
+ * out[0]: cells per lane; out[1]: lanes per workgroup; out[2]: tiles per XCD
+ * that run one work item before the next; out[3]: workgroups. */
+mcc_status mcc_debug_generated_launch(const mcc_mech *mech, int32_t kind, int64_t n_cells, int64_t ld, int64_t *out);
+
 /* Testing aid: sizes of the solver schedule, written to out[0..8]: LU
  * blocks, LU levels, Newton-matrix blocks, f-gather blocks of slots 0..3,
  * the size of the dense tail, and the wavefronts per SIMD of the solver

@@ -615,52 +615,76 @@ mcc_status mcc_cells_rate_constants(const mcc_cells *c, const double **k)
 constexpr int64_t kMallBytes = (int64_t)256 << 20;
 constexpr int kGeneratedArrays = 5;  // at most, of a generated kernel
 
-// Launches a generated kernel over cells [0, n_cells).  arrays: the kernel's
-// pointer arguments in order (null allowed for an unused output).  in_rows:
-// input rows the kernel reads per cell; streams: the kernel mostly writes and
-// gains from long runs of its reads once the inputs exceed the memory-side
-// cache.  72 species, 156 reactions, f/J kernel unless noted:
+enum GeneratedKind { kGenF = 0, kGenJ = 1, kGenFJ = 2, kGenVjp = 3 };
+
+// The shape of a generated kernel's launch over n_cells cells.
+struct GeneratedShape {
+    bool pair;      // two cells per lane
+    int threads;    // lanes of a tile, a workgroup
+    int grp;        // grp_tiles of the generated kernel's head
+    int64_t n_tiles, blocks;
+};
+
+// in_rows: input rows the kernel reads per cell.  The figures are of repeated
+// passes over the same arrays; 72 species, 156 reactions, f and J together
+// unless noted, us:
 // - up to 512 cells (eight tiles, one for each XCD): one cell per lane, the
-//   shorter chain (400 cells, in a graph: 3.5 us, two per lane 3.8);
+//   shorter chain (400 cells, in a graph: 3.5, two per lane 3.8);
 // - beyond, two cells per lane, whatever the rows' alignment (10,001 cells:
-//   23.9 us, one cell per lane 28.4);
+//   23.9, one cell per lane 28.4);
 // - an odd leading dimension: rows begin anywhere in a cache line, and the
 //   lines at a tile's ends, written by two tiles, cost more than the rest.
 //   256 lanes per workgroup once there are 64 such tiles or more (eight per
 //   XCD: the uneven rest is small) take three quarters of these ends away:
-//   130,001 cells 275 us, 64 lanes 301, one cell per lane 375; VJP kernel
-//   146, 156 and 187 us;
+//   130,001 cells 263, 64 lanes 295, one cell per lane 375 (on new arrays each
+//   pass 350).  The VJP kernel reads more than it writes, and its items share
+//   their rows through the XCD's L2 best in small tiles, so it does so only
+//   where the inputs do not stay in the memory-side cache: 130,001 cells 126,
+//   64 lanes 135; but 50,001 cells 36.9 and 35.4, of 150 species 72.5 and 64.8;
 // - even, inputs within the memory-side cache: 64 lanes, all items of a tile
 //   together (one fetch per tile, later items hit the XCD's L2): 100,000
-//   cells 131 us, 256 lanes 140;
-// - even, beyond it: the f/J kernel, whose reads are a fifth of its traffic,
-//   in groups of 32 tiles of 256 lanes, so that the first reads of every row
-//   are long runs (200,000 cells: 409 us, 128 tiles of 64 lanes 413, 64 lanes
-//   without groups 505); the VJP kernel, mostly reads, as within the cache
-//   (its items reuse the XCD's L2).
-static mcc_status launch_generated(hipFunction_t fn, hipFunction_t fn2, std::initializer_list<const void *> arrays,
-                                   int64_t n_cells, int64_t ld, int item_begin, int n_items, int in_rows,
-                                   bool streams, void *stream)
+//   cells 128, 256 lanes 135;
+// - even, beyond it: 256 lanes, whose first reads of a row are longer runs, and
+//   the kernels that write J, whose reads are a fifth of the traffic, in groups
+//   of 32 such tiles: 200,000 cells 385, ungrouped 431, 128 tiles of 64 lanes
+//   400, 64 lanes ungrouped 478; J alone 346, 330, 350, 329, but of 150 species,
+//   130,001 cells, 511, 563, 549, 606.  f alone, mostly reads, ungrouped: 131,
+//   grouped 132, 64 lanes 143; 150 species, 100,000 cells 126, 149, 135.  The VJP
+//   kernel as within the cache.
+static GeneratedShape generated_shape(GeneratedKind kind, int64_t n_cells, int64_t ld, int n_items, int in_rows)
+{
+    GeneratedShape g{};
+    const bool odd = ld % 2 != 0, beyond = 8 * (int64_t)in_rows * n_cells > kMallBytes;
+    g.pair = n_cells > 8 * kWave;
+    const int64_t lanes = g.pair ? (n_cells + 1) / 2 : n_cells;
+    const bool wide = odd ? lanes > 63 * 256 && (kind != kGenVjp || beyond) : beyond && kind != kGenVjp;
+    g.threads = wide ? 256 : kWave;
+    g.n_tiles = (lanes + g.threads - 1) / g.threads;
+    g.grp = !odd && beyond && (kind == kGenJ || kind == kGenFJ) ? (int)std::min<int64_t>(4, (g.n_tiles + 7) / 8) : 1;
+    g.blocks = (g.n_tiles + 8 * g.grp - 1) / (8 * g.grp) * 8 * g.grp * n_items;
+    return g;
+}
+
+// Launches a generated kernel (fn, its two-cell variant fn2) over cells
+// [0, n_cells).  arrays: the kernel's pointer arguments in order (null allowed
+// for an unused output).
+static mcc_status launch_generated(GeneratedKind kind, hipFunction_t fn, hipFunction_t fn2,
+                                   std::initializer_list<const void *> arrays, int64_t n_cells, int64_t ld,
+                                   int item_begin, int n_items, int in_rows, void *stream)
 {
     if (n_items == 0 || n_cells == 0) return ok();
     if (arrays.size() > kGeneratedArrays) return set_error(MCC_ERR_INVALID_ARG, "too many arrays");
-    const bool pair = n_cells > 8 * kWave, odd = ld % 2 != 0;
-    const int64_t lanes = pair ? (n_cells + 1) / 2 : n_cells;
-    const bool groups = !odd && streams && 8 * (int64_t)in_rows * n_cells > kMallBytes;
-    const int threads = groups || (odd && lanes > 63 * 256) ? 256 : kWave;
-    const int64_t n_tiles = (lanes + threads - 1) / threads;
-    const int grp = groups ? (int)std::min<int64_t>(4, (n_tiles + 7) / 8) : 1;
-    const int64_t blocks = (n_tiles + 8 * grp - 1) / (8 * grp) * 8 * grp * n_items;
-    if (blocks > 0x7fffffff) return set_error(MCC_ERR_INVALID_ARG, "too many cells for one launch");
+    const GeneratedShape g = generated_shape(kind, n_cells, ld, n_items, in_rows);
+    if (g.blocks > 0x7fffffff) return set_error(MCC_ERR_INVALID_ARG, "too many cells for one launch");
     long long nc = n_cells, ldl = ld;
-    int ib = item_begin, ni = n_items, nt = (int)n_tiles, shape = threads << 16 | grp;
+    int ib = item_begin, ni = n_items, nt = (int)g.n_tiles, shape = g.threads << 16 | g.grp;
     void *args[kGeneratedArrays + 6];
     int n_args = 0;
     for (const void *const &a : arrays) args[n_args++] = (void *)&a;
     for (void *a : {(void *)&nc, (void *)&ldl, (void *)&ib, (void *)&ni, (void *)&nt, (void *)&shape})
         args[n_args++] = a;
-    const hipError_t e = hipModuleLaunchKernel(pair ? fn2 : fn, (unsigned)blocks, 1, 1, (unsigned)threads, 1, 1, 0,
-                                               (hipStream_t)stream, args, nullptr);
+    const hipError_t e = hipModuleLaunchKernel(g.pair ? fn2 : fn, (unsigned)g.blocks, 1, 1, (unsigned)g.threads, 1, 1,
+                                               0, (hipStream_t)stream, args, nullptr);
     if (e != hipSuccess) return hip_error(e, "generated kernel launch");
     return ok();
 }
@@ -755,8 +779,8 @@ static mcc_status run_fj(const mcc_cells *c, const double *y, double *f, double 
     }
     mcc_status st = ensure_fj_module(c->mech);
     if (st != MCC_OK) return st;
-    return launch_generated(c->mech->fj_fn, c->mech->fj2_fn, {p.y, p.k, p.f, p.jac}, p.n_cells, p.ld, p.item_begin,
-                            p.n_items, t.N + t.R, true, stream);
+    return launch_generated(f && jac ? kGenFJ : f ? kGenF : kGenJ, c->mech->fj_fn, c->mech->fj2_fn,
+                            {p.y, p.k, p.f, p.jac}, p.n_cells, p.ld, p.item_begin, p.n_items, t.N + t.R, stream);
 }
 
 mcc_status mcc_calc_vjp(const mcc_cells *c, const double *y, const double *v, double *gy, double *glnk,
@@ -771,8 +795,24 @@ mcc_status mcc_calc_vjp(const mcc_cells *c, const double *y, const double *v, do
     DeviceGuard g(c->mech->device);
     mcc_status st = ensure_fj_module(c->mech);
     if (st != MCC_OK) return st;
-    return launch_generated(c->mech->vjp_fn, c->mech->vjp2_fn, {y, c->k, v, gy, glnk}, c->n_cells, c->ld, 0,
-                            (int)t.vjp_items.size(), 2 * t.N + t.R, false, stream);
+    return launch_generated(kGenVjp, c->mech->vjp_fn, c->mech->vjp2_fn, {y, c->k, v, gy, glnk}, c->n_cells, c->ld, 0,
+                            (int)t.vjp_items.size(), 2 * t.N + t.R, stream);
+}
+
+mcc_status mcc_debug_generated_launch(const mcc_mech *m, int32_t kind, int64_t n_cells, int64_t ld, int64_t *out)
+{
+    if (!m || !out) return set_error(MCC_ERR_INVALID_ARG, "null argument");
+    if (kind < kGenF || kind > kGenVjp || n_cells < 0 || n_cells > 0x7fffffff || ld < n_cells)
+        return set_error(MCC_ERR_INVALID_ARG, "need kind 0..3 and 0 <= n_cells <= ld");
+    const HostTables &t = m->t;
+    const int items = kind == kGenVjp ? (int)t.vjp_items.size()
+                                      : (kind != kGenJ ? t.n_fitems : 0) + (kind != kGenF ? t.n_jitems : 0);
+    const GeneratedShape g = generated_shape((GeneratedKind)kind, n_cells, ld, items, (kind == kGenVjp ? 2 : 1) * t.N + t.R);
+    out[0] = g.pair ? 2 : 1;
+    out[1] = g.threads;
+    out[2] = g.grp;
+    out[3] = g.blocks;
+    return ok();
 }
 
 mcc_status mcc_ablation_paper_deriv(const mcc_mech *m, int64_t n_cells, const double *y, const double *k,

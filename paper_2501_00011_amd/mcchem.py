@@ -74,6 +74,7 @@ def library(path: str = LIB_PATH) -> ctypes.CDLL:
         "mcc_mech_op_counts": ([vp, vp], ctypes.c_int),
         "mcc_debug_emulate_cell": ([vp, vp, vp, dbl, vp, vp, vp, vp], ctypes.c_int),
         "mcc_debug_schedule_info": ([vp, vp], ctypes.c_int),
+        "mcc_debug_generated_launch": ([vp, i32, i64, i64, vp], ctypes.c_int),
         "mcc_debug_solver_dispatch": ([vp, i64, i32, vp], ctypes.c_int),
         "mcc_debug_emulate_fj": ([vp, vp, vp, vp, vp, vp], ctypes.c_int),
         "mcc_debug_emulate_vjp": ([vp, vp, vp, vp, vp, vp, vp], ctypes.c_int),
@@ -273,6 +274,14 @@ class Mechanism:
         buf = (ctypes.c_int64 * 3)()
         _check(library().mcc_debug_solver_dispatch(self._h, int(n_cells), int(n_cu), ctypes.addressof(buf)))
         return dict(zip(("cells_per_wavefront", "state_doubles", "state_moved"), list(buf)))
+
+    def generated_launch(self, kind: str, n_cells: int, ld: int | None = None) -> dict:
+        """The shape of a generated kernel's launch ("f", "jac", "fj", "vjp")
+        (testing aid)."""
+        buf = (ctypes.c_int64 * 4)()
+        _check(library().mcc_debug_generated_launch(self._h, ("f", "jac", "fj", "vjp").index(kind), int(n_cells),
+                                                    int(n_cells if ld is None else ld), ctypes.addressof(buf)))
+        return dict(zip(("cells_per_lane", "lanes", "group", "workgroups"), list(buf)))
 
     def jac_pattern(self):
         rp = np.zeros(self.n_species + 1, dtype=np.int32)

@@ -39,3 +39,39 @@ def test_dispatch_arguments():
     for cells, n_cu in ((-1, 256), (1 << 31, 256), (10, -1)):
         with pytest.raises(mcchem.MccError, match="status 1"):
             h.solver_dispatch(cells, n_cu)
+
+
+def _lanes(h, kind, n_cells, ld=None):
+    g = h.generated_launch(kind, n_cells, ld)
+    assert g["workgroups"] * g["lanes"] * g["cells_per_lane"] >= n_cells
+    return g["lanes"], g["group"]
+
+
+@pytest.mark.parametrize("n,r", [(72, 156), (150, 350)])
+def test_generated_launches(n, r):
+    """One cell a lane up to 512 cells.  256-lane workgroups: odd leading
+    dimensions of 64 such tiles or more, for the VJP kernel only where its inputs
+    exceed the memory-side cache (50,001 cells of 150 species: 72.5 us with them,
+    64.8 with 64 lanes); even ones beyond that cache, grouped where J is written
+    (f alone, 100,000 cells of 150 species: 149 us grouped, 126 not); not for the
+    VJP kernel."""
+    h = mcchem.Mechanism(synth.make_mechanism(n, r), device=-1)
+    for kind in ("f", "jac", "fj", "vjp"):
+        assert h.generated_launch(kind, 512)["cells_per_lane"] == 1
+        assert h.generated_launch(kind, 513)["cells_per_lane"] == 2
+        rows = r + (2 * n if kind == "vjp" else n)
+        fits = (256 << 20) // (8 * rows)  # cells whose inputs the cache holds
+        odd = fits | 1
+        first_wide = 2 * 63 * 256 + 1
+        assert first_wide < fits
+        assert _lanes(h, kind, first_wide - 2, first_wide - 2 | 1) == (64, 1)
+        assert _lanes(h, kind, first_wide, first_wide) == ((64, 1) if kind == "vjp" else (256, 1))
+        assert _lanes(h, kind, odd - 2) == ((64, 1) if kind == "vjp" else (256, 1))
+        assert _lanes(h, kind, odd + 2) == (256, 1)
+        even = fits // 2 * 2
+        assert _lanes(h, kind, even) == (64, 1)
+        wide = {"f": (256, 1), "jac": (256, 4), "fj": (256, 4), "vjp": (64, 1)}[kind]
+        assert _lanes(h, kind, even + 2) == wide and _lanes(h, kind, 400000) == wide
+    for args in ((0, -1, 5), (0, 6, 5), (0, 1 << 31, 1 << 31)):
+        with pytest.raises(mcchem.MccError, match="status 1"):
+            h.generated_launch(("f",)[args[0]], args[1], args[2])

@@ -101,3 +101,29 @@ def test_rows_in_parts(torch):
     h = mcchem.Mechanism(m)
     c = synth.make_cells(m, 1025, seed=43)
     _check(torch, m, h, c, 1027, 1)
+
+
+@pytest.mark.parametrize("pad", [0, 1])
+def test_f_alone_beyond_the_cache(torch, pad):
+    """Inputs that exceed the memory-side cache (30 rows of 1.2 million cells):
+    f alone runs in other workgroups than f and J together, with the same bits."""
+    m = synth.make_mechanism(10, 20)
+    h = mcchem.Mechanism(m)
+    C = 1_200_001 + pad  # an odd and an even leading dimension
+    few = synth.make_cells(m, 1009, seed=47)
+    dev = torch.device("cuda:0")
+    of = torch.arange(C, device=dev) % 1009
+    up = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(dev)[..., of].contiguous()  # noqa: E731
+    b = mcchem.Cells(h, C)
+    b.bind(up(few.T), up(few.P), up(few.jscale))
+    y = up(few.y0)
+    f = torch.full_like(y, float("nan"))
+    b.deriv(y, f)
+    f2, _ = b.deriv_jac(y)
+    torch.cuda.synchronize()
+    assert torch.equal(f, f2)
+    o = pytest.importorskip("oracle").Oracle(m)
+    fr, fs = o.deriv(o.rate_constants(few.T, few.jscale), few.y0)
+    assert np.all(np.abs(f[:, :1009].cpu().numpy() - fr) <= 1e-12 * fs)
+    assert torch.equal(f, f[:, :1009].contiguous()[:, of])
+    b.close()

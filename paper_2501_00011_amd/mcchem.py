@@ -557,7 +557,8 @@ def autotune_solver(mech, cells, dt: float, opts: SolverOpts | None = None, devi
     """Pick the solver build and the cell schedule for `mech` by measurement.
     Every admissible combination of dense-tail size (`candidates`) and
     register budget (`waves`: 0 the library's choice, 1 one wavefront per
-    SIMD) is compiled; for each, one outer step of the sample `cells` (a
+    SIMD; where the sample runs four cells to a wavefront, which has one
+    build, the library's choice alone) is compiled; for each, one outer step of the sample `cells` (a
     synth.Cells) runs untimed to produce per-cell counters, then one timed
     step per schedule (`schedules`: the identity, longest first by those
     counters, zigzag) with HIP events, best of `reps`.  The choices change
@@ -575,7 +576,18 @@ def autotune_solver(mech, cells, dt: float, opts: SolverOpts | None = None, devi
     for m_tail in candidates:
         if m_tail > mech.n_species:
             continue
-        for w in waves:
+        budgets = waves
+        if len(waves) > 1:
+            # timing one kernel once for each budget would pick a budget by noise,
+            # which smaller batches, on the one-cell kernels, then run with
+            try:
+                h = Mechanism(mech, device=device, dense_tail=m_tail)
+            except MccError:
+                continue
+            if h.solver_dispatch(cells.n_cells)["cells_per_wavefront"] > 1:
+                budgets = (0,)
+            h.close()
+        for w in budgets:
             try:
                 h = Mechanism(mech, device=device, dense_tail=m_tail, waves_per_simd=w)
             except MccError:

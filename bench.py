@@ -85,20 +85,20 @@ def issue_roofline(launch_s, n_cells, dense_tail):
             "frac": achieved / VALU_ISSUE_PEAK, "instructions_per_launch": insts}
 
 
-def per_launch_state(sn, K, n_species, mech):
+def per_launch_state(sn, K, mech, n_cu=0):
     """HBM bytes the per-launch form moves for the solver state in one outer
     step: a cell takes part in about L = ceil(steps / K) launches, writes
-    its state (backward differences [8][NS x 64] and 16 scalars, doubles)
-    at the end of all but the last and reads it at the start of all but the
-    first.  None for one launch."""
+    its state (the backward differences and scalars of the kernel that takes
+    the batch) at the end of all but the last and reads it at the start of all
+    but the first.  None for one launch.  n_cu: compute units, 0 those of
+    the mechanism's device."""
     if K <= 0:
         return None
     import numpy as np
-    ns = len([b for b in mech.schedule_info()["fg_blocks"] if b > 0]) or 1
-    state_bytes = 8 * (8 * ns * 64 + 24)
+    d = mech.solver_dispatch(len(sn["steps"]), n_cu)
     launches = np.ceil(sn["steps"].astype(np.float64) / K)
-    return {"state_bytes_per_cell": state_bytes, "launches_max": int(launches.max()),
-            "bytes_per_outer_step": float(2 * state_bytes * np.maximum(launches - 1, 0).sum())}
+    return {"state_bytes_per_cell": 8 * d["state_moved"], "launches_max": int(launches.max()),
+            "bytes_per_outer_step": float(2 * 8 * d["state_moved"] * np.maximum(launches - 1, 0).sum())}
 
 
 def parse():
@@ -829,7 +829,7 @@ def main():
                          "launch_us": vj_s * 1e6, "bytes_per_cell": vj_bytes,
                          "launch_us_eager": vj_eager_s * 1e6,
                          "timing": "20 launches in a HIP graph" if vj_graph_s is not None else "eager"},
-        "per_launch_state": per_launch_state(sn, args.steps_per_launch, m.n_species, mech),
+        "per_launch_state": per_launch_state(sn, args.steps_per_launch, mech),
         "solver": {"failed_cells": int((st != 0).sum()),
                    "steps_mean": float(sn["steps"].mean()), "steps_max": int(sn["steps"].max()),
                    "steps_percentiles": {str(q): float(np.percentile(sn["steps"], q)) for q in (1, 10, 50, 90, 99)},

@@ -1,4 +1,5 @@
 """Which kernel a batch gets (host logic, no GPU)."""
+import numpy as np
 import pytest
 
 from paper_2501_00011_amd import mcchem, synth
@@ -30,6 +31,29 @@ def test_shapes_of_one_solver():
     for n, r, tail in ((72, 144, 48), (72, 144, 0), (20, 129, 0), (96, 201, 32), (150, 350, 64)):
         h = mcchem.Mechanism(synth.make_mechanism(n, r), device=-1, dense_tail=tail)
         assert _cells_per_wavefront(h, 1) == _cells_per_wavefront(h, 100000) == 1
+
+
+@pytest.mark.parametrize("n,tail,cells,doubles", [
+    (72, 32, 10000, 7 * 5 * 16 + 16),   # four cells a wavefront: 7 differences in 3 + 2 blocks of 16 rows
+    (72, 32, 1000, 8 * 2 * 64 + 15),    # one cell a wavefront: 8 differences in two slots of 64
+    (20, 0, 10, 7 * 2 * 16 + 16),
+    (150, 64, 10, 8 * 3 * 64 + 15),
+])
+def test_state_of_the_per_launch_form(n, tail, cells, doubles):
+    """What the benchmark counts as moved between launches is what the kernel
+    that takes the batch reads and writes: a cell of s steps in launches of K
+    writes its state ceil(s / K) - 1 times, and it is read as often."""
+    import bench
+    h = mcchem.Mechanism(synth.make_mechanism(n, 2 * n), device=-1, dense_tail=tail)
+    d = h.solver_dispatch(cells, 256)
+    assert d["state_moved"] == doubles <= d["state_doubles"]
+    sn = np.zeros(cells, dtype=mcchem.STATS_DTYPE)
+    sn["steps"] = 10
+    sn["steps"][0] = 11
+    got = bench.per_launch_state(sn, 5, h, 256)
+    assert got == {"state_bytes_per_cell": 8 * doubles, "launches_max": 3,
+                   "bytes_per_outer_step": 2.0 * 8 * doubles * (cells + 1)}
+    assert bench.per_launch_state(sn, 0, h, 256) is None
 
 
 def test_dispatch_arguments():

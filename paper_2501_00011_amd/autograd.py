@@ -61,21 +61,8 @@ class _SolveStep(torch.autograd.Function):
         k = torch.exp(lnk).contiguous()
         cells.set_rate_constants(k)
         y0 = y0.contiguous()
-        C, N = cells.n_cells, cells.mech.n_species
-        tape_len = torch.empty(C, dtype=torch.int64, device=y0.device)
-        tape = _first_tape(C, N, stride, y0.device)
-        while True:
-            y = y0.clone()
-            status, _ = cells.step_taped(y, dt, tape, tape_len, opts)
-            shortest, longest = torch.stack(torch.aminmax(tape_len)).tolist() if C else (0, 0)
-            if shortest >= 0:
-                break
-            need = 2 * tape.shape[1]  # a tape did not fit: the same step again with room for it
-            del tape
-            tape = torch.empty((C, need), dtype=torch.float64, device=y0.device)
+        y, status, tape, tape_len = _taped_step(cells, y0, dt, opts, stride)
         _check_forward(status)
-        if stride is None and 2 * longest < tape.shape[1]:
-            tape = tape[:, :longest].contiguous()  # what is kept until backward: the steps taken
         ctx.save_for_backward(y0, k, tape, tape_len)
         ctx.cells = cells
         return y
@@ -97,25 +84,55 @@ def solve_step(cells: "mcchem.Cells", y0: torch.Tensor, lnk: torch.Tensor, dt: f
                opts: "mcchem.SolverOpts | None" = None, tape_stride: int | None = None) -> torch.Tensor:
     """y(dt) [N][ld] from y0 [N][ld] with rate constants exp(lnk) [R][ld].
     tape_stride: doubles of step tape per cell (default room for 256 to 4096
-    steps, by the number of cells, cut to the longest tape afterwards; doubled and
-    the step redone when a tape does not fit)."""
+    steps, by the number of cells; doubled and the step redone when a tape does
+    not fit; cut to the longest tape afterwards if room for 256 steps and its
+    doublings would have been less)."""
     return _SolveStep.apply(y0, lnk, cells, dt, opts, tape_stride or None)
 
 
-def _first_tape(n_cells: int, n_species: int, stride: "int | None", device) -> torch.Tensor:
-    """The tape of the first attempt.  A second attempt costs a whole solve, the
-    cut to the longest tape only a copy (72 species, 1,000 cells, forward and
-    backward pass: 76 ms, and 170 ms with room for 256 steps and two
-    doublings), so it starts with room for 4,096 steps, at most 2 GiB in all
-    and at least 256 steps, and with the 256 alone where memory is short."""
-    if stride is not None:
-        return torch.empty((n_cells, stride), dtype=torch.float64, device=device)
-    per_step = n_species + 16
-    steps = min(4096, max(256, (2 << 30) // (8 * max(n_cells, 1) * per_step)))
-    try:
-        return torch.empty((n_cells, 4 + steps * per_step), dtype=torch.float64, device=device)
-    except torch.cuda.OutOfMemoryError:
-        return torch.empty((n_cells, 4 + 256 * per_step), dtype=torch.float64, device=device)
+def _first_steps(n_cells: int, n_species: int) -> int:
+    """Steps that the first tape has room for.  A second attempt costs a whole
+    solve, the cut to the longest tape only a copy (72 species, 1,000 cells,
+    forward and backward pass: 73 ms, and 153 ms with room for 256 steps and two
+    doublings), so the first has room for 4,096 steps, at most 2 GiB in all and
+    at least 256 steps (10,000 cells of 72 species: 305 steps, and doublings)."""
+    return min(4096, max(256, (2 << 30) // (8 * max(n_cells, 1) * (n_species + 16))))
+
+
+def _doubled(width: int, need: int) -> int:
+    while width < need:
+        width *= 2
+    return width
+
+
+def _taped_step(cells, y0, dt, opts, stride):
+    """One taped outer step, again with a wider tape while one does not fit.
+    The tape that is kept is no wider than doublings of `least` make it, and
+    where memory is too short for more than these, they are what is taken."""
+    C, N, dev = cells.n_cells, cells.mech.n_species, y0.device
+    tape_len = torch.empty(C, dtype=torch.int64, device=dev)
+    least = stride or 4 + 256 * (N + 16)
+    width = stride or 4 + _first_steps(C, N) * (N + 16)
+    roomy, need = width > least, least
+    while True:
+        tape = None
+        try:
+            tape = torch.empty((C, width), dtype=torch.float64, device=dev)
+            y = y0.clone()
+            status, _ = cells.step_taped(y, dt, tape, tape_len, opts)
+            shortest, longest = torch.stack(torch.aminmax(tape_len)).tolist() if C else (0, 0)
+            if shortest >= 0:
+                need = longest
+                if roomy and width > _doubled(least, longest):
+                    whole, tape = tape, torch.empty((C, longest), dtype=torch.float64, device=dev)
+                    tape.copy_(whole[:, :longest])
+                return y, status, tape, tape_len
+            need = width + 1
+            width *= 2
+        except torch.cuda.OutOfMemoryError:
+            if not roomy:
+                raise
+            roomy, width, whole = False, _doubled(least, need), None
 
 
 def _tape_bound(stats, n_species: int) -> int:

@@ -182,53 +182,41 @@ void build_quad(const mcc_mech_desc *d, const std::vector<std::vector<char>> &lp
     // scratch into its fill.
     const int tm = (kMaxOrder + 1) * (kMaxOrder + 1);
     std::vector<std::vector<int>> at(N, std::vector<int>(N, -1));
-    std::vector<std::vector<char>> staged_at(N, std::vector<char>(N, 0));
     int lu_end = 0, scratch = 0, n_first = 0, n_second = 0;  // ends of the regions
     std::vector<int> fills[2];
     std::map<std::pair<int, int>, int> staged;
-    // whether a pivot before k updates entry (i, j)
-    auto before = [&](int i, int j, int k) {
-        for (int x = 0; x < std::min({i, j, k}); ++x)
-            if (lp[i][x] && lp[x][j]) return true;
-        return false;
-    };
-    auto layout = [&](int split) {
-        for (auto &r : at) std::fill(r.begin(), r.end(), -1);
-        fills[0].clear();
-        fills[1].clear();
-        staged.clear();
-        int n = kQFirst;
-        for (int part = 0; part < 2; ++part) {
-            for (int fill = 0; fill < 2; ++fill)
-                for (int i = 0; i < N; ++i)
-                    for (int j = 0; j < N; ++j)
-                        if (lp[i][j] && std::min(i, j) < F && (std::min(i, j) >= split) == (part == 1) &&
-                            (int)!jac.count({i, j}) == fill) {
-                            if (fill && before(i, j, q.m0)) fills[part].push_back(n);
-                            at[i][j] = n++;
-                        }
-            if (part == 0) n_first = n;
+    // the first pivot that updates entry (i, j), if any; whether one before k does
+    std::vector<std::vector<int>> updates(N, std::vector<int>(N, N));
+    for (int x = N - 1; x >= 0; --x)
+        for (int i = x + 1; i < N; ++i)
+            if (lp[i][x])
+                for (int j = x + 1; j < N; ++j)
+                    if (lp[x][j]) updates[i][j] = x;
+    auto before = [&](int i, int j, int k) { return updates[i][j] < k; };
+    std::vector<std::vector<char>> assembled(N, std::vector<char>(N, 0));
+    for (const auto &kv : jac) assembled[kv.first.first][kv.first.second] = 1;
+    // Entries by the smaller of row and column, the front's with those that are
+    // assembled; the tail's by whether they are, or the first pivot that updates them.
+    std::vector<int> front_at(N + 1, 0), front_assembled(N + 1, 0), tail_at_pivot(N + 1, 0);
+    int tail_assembled = 0;
+    for (int i = 0; i < N; ++i)
+        for (int j = 0; j < N; ++j) {
+            if (std::min(i, j) < F && lp[i][j]) {
+                front_at[std::min(i, j)]++;
+                front_assembled[std::min(i, j)] += assembled[i][j];
+            } else if (i >= F && j >= F) {
+                if (assembled[i][j]) tail_assembled++;
+                else tail_at_pivot[updates[i][j]]++;
+            }
         }
-        n_second = n;
-        int n_held = n_first;
-        for (const auto &kv : jac)
-            if (at[kv.first.first][kv.first.second] >= n_first)
-                n_held = std::max(n_held, at[kv.first.first][kv.first.second] + 1);
-        // tail entries of the Jacobian, and those the first part's pivots update
-        for (auto &r : staged_at) std::fill(r.begin(), r.end(), 0);
-        for (const auto &kv : jac)
-            if (kv.first.first >= F && kv.first.second >= F) staged_at[kv.first.first][kv.first.second] = 1;
-        for (int k = 0; k < split; ++k)
-            for (int i = F; i < N; ++i)
-                for (int j = F; j < N; ++j)
-                    if (lp[i][k] && lp[k][j] && !staged_at[i][j]) staged_at[i][j] = 2;
-        int ns = n_first;
-        for (int i = F; i < N; ++i)
-            for (int j = F; j < N; ++j)
-                if (staged_at[i][j]) {
-                    if (staged_at[i][j] == 2) fills[0].push_back(ns);
-                    staged[{i, j}] = ns++;
-                }
+    const int n_front = std::accumulate(front_at.begin(), front_at.end(), 0);
+    // Sets the ends of the regions for a split; returns the doubles they take.
+    auto size = [&](int split) {
+        const auto upto = [&](const std::vector<int> &v) { return std::accumulate(v.begin(), v.begin() + split, 0); };
+        n_first = kQFirst + upto(front_at);
+        n_second = kQFirst + n_front;
+        const int n_held = n_first + std::accumulate(front_assembled.begin() + split, front_assembled.end(), 0);
+        const int ns = n_first + tail_assembled + upto(tail_at_pivot);
         lu_end = std::max(n_second, ns);
         const int held = std::max(n_held, ns);  // the partials stay above this
         scratch = std::max({R, tm, P - (lu_end - held)});
@@ -240,14 +228,33 @@ void build_quad(const mcc_mech_desc *d, const std::vector<std::vector<char>> &lp
     // dense update of the tail in registers (64 multiply-adds, any pivot).
     q.split = 0;
     q.m0 = std::max(0, F - L);
-    const int room = layout(0);
+    const int room = size(0);
     for (int k = 0; k < q.m0; ++k) {
         int r = 0, cc = 0;
         for (int i = F; i < N; ++i) r += lp[i][k], cc += lp[k][i];
-        if (r * cc > 160 || layout(k + 1) > room) break;
+        if (r * cc > 160 || size(k + 1) > room) break;
         q.split = k + 1;
     }
-    layout(q.split);
+    size(q.split);
+    {
+        int n = kQFirst;
+        for (int part = 0; part < 2; ++part)
+            for (int fill = 0; fill < 2; ++fill)
+                for (int i = 0; i < N; ++i)
+                    for (int j = 0; j < N; ++j)
+                        if (lp[i][j] && std::min(i, j) < F && (std::min(i, j) >= q.split) == (part == 1) &&
+                            (assembled[i][j] == 0) == (fill == 1)) {
+                            if (fill && before(i, j, q.m0)) fills[part].push_back(n);
+                            at[i][j] = n++;
+                        }
+        int ns = n_first;  // tail entries of the Jacobian, and those the first part's pivots update
+        for (int i = F; i < N; ++i)
+            for (int j = F; j < N; ++j)
+                if (assembled[i][j] || before(i, j, q.split)) {
+                    if (!assembled[i][j]) fills[0].push_back(ns);
+                    staged[{i, j}] = ns++;
+                }
+    }
     q.off_r = lu_end;
     const int off_p = lu_end + scratch - P;
     q.off_y = lu_end + scratch;
@@ -438,7 +445,7 @@ void build_quad(const mcc_mech_desc *d, const std::vector<std::vector<char>> &lp
                 const size_t w = ((size_t)(e / 8) * L + i) * 8 + e % 8;
                 if (u && row == N && mc == i) q.mid_load[w] = (uint16_t)kQOne;  // beyond the front: an identity row
                 if (row >= N || col >= N || !lp[row][col]) continue;
-                if (jac.count({row, col}) || before(row, col, q.m0)) q.mid_load[w] = (uint16_t)at[row][col];
+                if (assembled[row][col] || before(row, col, q.m0)) q.mid_load[w] = (uint16_t)at[row][col];
                 q.mid_store[w] = (uint16_t)at[row][col];
             }
     }

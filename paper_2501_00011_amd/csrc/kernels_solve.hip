@@ -639,13 +639,12 @@ struct Cell {
     // pass through local memory; a factorised column is final on every row
     // (rows above the panel: U, which the accumulators took up from the row
     // phase), and each lane keeps its row of it in S, where the triangular
-    // solves read it.   The same
-    // bits as with the block in local memory.  64 rows, one attempt of 150
-    // species 155 -> 128 us and three cells a compute unit instead of two (1,000
-    // cells 281 -> 214 ms), of 110 species 65 -> 52 us and eight instead of
-    // three (108 -> 63 ms); 48 rows, 72 species, 39 -> 32 us and eight instead
-    // of six (1,003 cells 38.5 -> 30.5 ms, 10,000 cells 195 -> 130); 32 rows, 72
-    // species, 8 cells 26.9 -> 25.3 ms, 10,000 cells 161 -> 139.
+    // solves read it.  The same
+    // bits as with the block in local memory.  64 rows, 150 species: three
+    // cells a compute unit instead of two, 1,000 cells 281 -> 208 ms; 110
+    // species: eight instead of three, 108 -> 58 ms; 48 rows, 72 species: eight
+    // instead of six, 1,003 cells 42.9 -> 33.5 ms, 10,000 cells 195 -> 128; 32
+    // rows, 72 species, 8 cells 25.4 -> 23.4 ms, 2,048 cells 52.2 -> 40.8.
     __device__ __forceinline__ bool register_tail()
     {
         KParams &p = params_here();

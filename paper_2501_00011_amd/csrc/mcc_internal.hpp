@@ -105,7 +105,7 @@ struct VjpItem {
 constexpr int kVjpRoundLoads = 64;  // measured: 48-96 beat 16-32 at 200k cells, equal at 10k
 
 // ---------------------------------------------------------------------------
-// Tables of the four-cells-per-wavefront solver (kernels_quad.hip): a cell is
+// Tables of the four-cells-per-wavefront solver (quad_tables.hpp): a cell is
 // a row of 16 lanes, and every table is laid out for 16 lanes, shared by the
 // four cells.  Rows of the system live in blocks of 16: block f < FB holds the
 // front positions 16 f .. 16 f + 15, block FB + b the rows of the dense tail
@@ -371,7 +371,7 @@ constexpr int kStateScalars = 24;
 // [0] .. [11], [13], [14], [16] and [17].
 constexpr int kOneStateScalars = 15, kQuadStateScalars = 16;
 
-// Kernel parameters of the quad solver (kernels_quad.hip); the fields from
+// Kernel parameters of the quad solver (quad_kernel.hpp); the fields from
 // `order` on mean what they do in SolveParams.
 struct QuadParams {
     const int32_t *vsp;

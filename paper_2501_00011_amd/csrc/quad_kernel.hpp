@@ -26,6 +26,19 @@
 // issuing at most one per four, and about 35,000 cycles of waits on dependent
 // local-memory reads and table fetches.
 //
+// Spilled registers.  The tail, the middle pivots' multipliers and the state
+// are more than a wavefront's 512 registers (256 without a front, two
+// wavefronts on a SIMD): 36 to 187 of them spill behind a front, 83 for 72
+// species, none to 119 without.  A spill saves and restores each lane's own
+// value, under the branch it stands in.  That is safe here because nothing that
+// reads other lanes (DPP, ballots, readlane) stands in a branch that divides a
+// row: conditions around it are values of the cell, the same on a row's 16
+// lanes, and DPP stays within the row.  The assembly below begins with the wait
+// states a DPP source needs after any write, a reload's among them.  The taping
+// build is allocated apart (132 spills for 72 species): the tests ask for the same
+// bits from both, in every shape.  (A reverse-mode build of kernels_solve.hip
+// that spilled once gave wrong sums for a reason not found; it is refused there.)
+//
 // The four cells of a wavefront take their step attempts together.  Whatever
 // differs between them -- step size, order, acceptance, the end of the outer
 // step -- is a per-lane value, equal on a row's 16 lanes; a finished cell's

@@ -127,3 +127,14 @@ def test_f_alone_beyond_the_cache(torch, pad):
     assert np.all(np.abs(f[:, :1009].cpu().numpy() - fr) <= 1e-12 * fs)
     assert torch.equal(f, f[:, :1009].contiguous()[:, of])
     b.close()
+
+
+@pytest.mark.parametrize("cells,ld", [(1333, 1334), (1334, 1334), (1333, 1333), (1334, 1335)])
+def test_two_cells_a_lane_72_species(torch, cells, ld):
+    """The 72-species mechanism, whose VJP kernel has items of many rows, beyond
+    512 cells: whole pairs and a shifted last one, even and odd rows."""
+    m, c, _ = synth.workload("medium10k", cells)
+    h = mcchem.Mechanism(m)
+    for kind in ("fj", "vjp"):
+        assert h.generated_launch(kind, cells, ld)["cells_per_lane"] == 2
+    _check(torch, m, h, c, ld, 0)

@@ -73,8 +73,8 @@ def within(y, ref):
     return bool(np.all(np.abs(y - ref) <= 1e-6 * np.abs(ref) + 1e2))
 
 
-# one block of front positions nearly empty and half full, three, four
-@pytest.fixture(scope="module", params=[33, 40, 72, 88])
+# one to four blocks of front positions: the last one full, nearly empty, in between
+@pytest.fixture(scope="module", params=[33, 36, 48, 49, 64, 65, 72, 80, 81, 88])
 def copies(request, oracle_mod):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")

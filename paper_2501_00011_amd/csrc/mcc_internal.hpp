@@ -275,9 +275,8 @@ struct HostTables {
     QuadTables quad;                  // four-cells-per-wavefront solver (quad.ok: it takes this shape)
 };
 
-// Fills t->quad from the compiled order and the symbolic factors (lp, by
-// position, the tail block dense), for the shapes that solver takes.
-void build_quad(const mcc_mech_desc *d, const std::vector<std::vector<char>> &lp, HostTables *t);
+// Fills t->quad from the compiled order, for the shapes that solver takes.
+void build_quad(const mcc_mech_desc *d, HostTables *t);
 // Host emulation of the quad solver's phases for one cell (testing aid), as emulate_cell.
 int emulate_quad(const HostTables &t, const double *k, const double *y_species, double c, const double *b_species,
                  double *f_species, double *x_species);

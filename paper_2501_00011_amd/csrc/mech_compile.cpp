@@ -762,7 +762,7 @@ mcc_status compile_mechanism(const mcc_mech_desc *d, int dense_tail, HostTables 
         oc.reserved = 0;
     }
 
-    build_quad(d, lp, t);
+    build_quad(d, t);
     return MCC_OK;
 }
 

@@ -130,7 +130,7 @@ void emit_nm(std::vector<NmEntry> es, std::vector<QNmRec> *recs, int *n_recs, in
 
 }  // namespace
 
-void build_quad(const mcc_mech_desc *d, const std::vector<std::vector<char>> &lp0, HostTables *t)
+void build_quad(const mcc_mech_desc *d, HostTables *t)
 {
     QuadTables &q = t->quad;
     q = QuadTables{};
@@ -159,10 +159,6 @@ void build_quad(const mcc_mech_desc *d, const std::vector<std::vector<char>> &lp
     q.vsp.assign((size_t)q.NB * L, -1);
     for (int p = 0; p < N; ++p) q.vsp[(size_t)block_of(p) * L + lane_of(p)] = t->perm[p];
 
-    std::vector<std::vector<char>> lp = lp0;
-    for (int i = F; i < N; ++i)
-        for (int j = F; j < N; ++j) lp[i][j] = 1;
-
     // ---- partials and Jacobian terms per entry (positions) ------------------
     struct Part { int j, slot, s; };
     std::vector<Part> parts;
@@ -174,6 +170,20 @@ void build_quad(const mcc_mech_desc *d, const std::vector<std::vector<char>> &lp
     for (int a = 0; a < P; ++a)
         for (const auto &kv : net(d, parts[a].j))
             if (kv.second != 0.0) jac[{t->iperm[kv.first], t->iperm[parts[a].s]}].push_back({kv.second, a});
+
+    // The factors' entries: those with a term, and what the elimination fills.
+    // (Not the pattern of the Jacobian, which counts every participant of a
+    // reaction: a species that it needs and gives back, or a product of yield
+    // zero, has no term there, and an entry that is neither assembled nor
+    // updated would be read without a value.)
+    std::vector<std::vector<char>> lp(N, std::vector<char>(N, 0));
+    for (const auto &kv : jac) lp[kv.first.first][kv.first.second] = 1;
+    for (int i = F; i < N; ++i)
+        for (int j = F; j < N; ++j) lp[i][j] = 1;
+    for (int k = 0; k < F; ++k)
+        for (int i = k + 1; i < N; ++i)
+            if (lp[i][k])
+                for (int j = k + 1; j < N; ++j) lp[i][j] |= lp[k][j];
 
     // ---- local memory -------------------------------------------------------
     // [fixed cells][entries of the first part][of the second, fill last]

@@ -476,7 +476,8 @@ mcc_status mcc_adjoint_step(const mcc_cells *cells, const double *y0, const doub
 
 /* Cell schedule of the per-cell solver kernels (mcc_solve_step and its
  * per-launch and taped forms, mcc_adjoint_step, mcc_replay_step): workgroup i
- * integrates cell order[i], so cells listed first start first.  Cells whose
+ * integrates cell order[i], or order[4 i] to order[4 i + 3] where four cells
+ * share a wavefront, so cells listed first start first.  Cells whose
  * integrations take many steps listed first shorten the tail of a launch
  * (longest-processing-time-first); the per-cell counters of the previous
  * outer step (mcc_cell_stats) predict them.  order: host int32 [n_cells], a

@@ -271,10 +271,12 @@ void build_quad(const mcc_mech_desc *d, HostTables *t)
     const int total = q.off_y + F + q.TB * L;
     q.stride = (total + 15) / 16 * 16;
     if (q.stride / 16 % 2 == 0) q.stride += 16;  // an odd multiple of 16 doubles: neighbour cells start on other banks
-    // Three wavefronts' cells have to fit a compute unit's local memory: with
-    // 12 to 16 cells there the solve of 10,000 cells took 135 ms against 163 ms
-    // of the one-cell kernels (72 species, 151 reactions, tail of 32), with 8
-    // cells 601 ms against 505 ms (96 species, 201 reactions).
+    // Three wavefronts' cells have to fit a compute unit's local memory.  One
+    // cell / four cells a wavefront, ms, 10,000 cells: with 16 cells there 123 /
+    // 93 (72 species, 136 reactions), 135 / 98 (80, 136); with 12, 141 / 128 (72,
+    // 151), 165 / 164 (84, 159), 158 / 154 (88, 132), 146 / 136 (96, 144), and
+    // 4,000 cells, a second round on 256 compute units, 69.5 / 66.9, 77.9 / 88.4,
+    // 80.1 / 84.4, 73.9 / 74.9; with 8 cells 505 / 601 (96, 201).
     if ((int64_t)q.stride * 8 * kQCells * 3 > kQLdsBytes) return;
     auto yid = [&](int species) { return q.off_y + t->iperm[species]; };
 

@@ -203,3 +203,46 @@ def test_tables_cost_little_to_build():
         mcchem.Mechanism(m, device=-1, dense_tail=tail).close()
         best[tail] = min(best.get(tail, 9.0), time.process_time() - t)
     assert best[32] <= 3.0 * best[48], best
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,tail,cells", [(20, 0, 9), (32, 0, 4), (40, 0, 9), (72, 48, 9)])
+def test_multicell_failures(n, tail, cells):
+    """What stops the one system stops every cell, where the oracle's stops: a
+    work limit, a Newton iteration that cannot converge, a non-finite state in
+    one cell (nothing is written then).  A call after that is as the first."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    oracle = pytest.importorskip("oracle")
+    dev = torch.device("cuda:0")
+    m = synth.make_mechanism(n, 2 * n)
+    h = mcchem.Mechanism(m, dense_tail=tail)
+    c = synth.make_cells(m, cells, seed=950 + n)
+    o = oracle.Oracle(m)
+    k = o.rate_constants(c.T, c.jscale)
+    up = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(dev)  # noqa: E731
+    b = mcchem.Cells(h, cells)
+    b.bind(up(c.T), up(c.P), up(c.jscale))
+
+    def step(y0, **kw):
+        y = up(y0)
+        st, stats = b.step_multicell(y, 5.0, mcchem.default_opts(**kw))
+        torch.cuda.synchronize()
+        return y.cpu().numpy(), st.cpu().numpy(), mcchem.stats_numpy(stats)
+
+    first = step(c.y0)
+    for kw, status in ((dict(max_steps=1), 1), (dict(max_steps=30), 1), (dict(max_newton=1, h_min_rel=1e-12), 2)):
+        print(f"Multi-cells: {n} species, {cells} cells, {kw}", flush=True)
+        yo, so, sto = o.solve_multicell(k, c.y0, 5.0, oracle.default_opts(**kw))
+        y, st, sn = step(c.y0, **kw)
+        assert so == status and np.all(st == status)
+        assert np.all(sn["newton_fails"] == sto["newton_fails"]) and np.all(sn["steps"] == sto["steps"])
+        assert np.all(np.abs(y - yo) <= 1e-6 * np.abs(yo) + 1e2)
+    sick = c.y0.copy()
+    sick[n // 2, cells - 1] = np.nan
+    y, st, _ = step(sick)
+    assert np.all(st == 4) and np.array_equal(y, sick, equal_nan=True)
+    again = step(c.y0)
+    assert all(np.array_equal(p, q) for p, q in zip(first, again))
+    b.close()
